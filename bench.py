@@ -173,7 +173,7 @@ def reached_arcs(g, sources):
 def graphs_bench(args) -> int:
     """graphs-mix: 16 small R-MAT graphs (scales 10-12, edge factor 16, 64
     sources each) in one bc_run_graphs call per step (BC_LOOP_AUTO picks the
-    graphs whose batches share one device-resident launch), against one
+    graphs whose sources share one device-resident launch), against one
     bc_run_async call per graph (BC_MODE_AUTO) on the same sources.  GTEPS =
     sum of k * nnz over the graphs / step time."""
     import numpy as np
@@ -743,12 +743,13 @@ def main() -> int:
     def roofline_of(prof, path, ms_step, steps):
         """Dominant kernel of a profile and its roofline point."""
         if prof["fused"]["launches"]:
-            # device-resident level loop: one launch runs whole batches, forward
-            # and reverse; its bytes are both passes' work counters
+            # device-resident level loop: one launch runs whole sources, forward
+            # and reverse; its bytes are both passes' work counters (the
+            # one-source model: no lane words)
             pc = prof["fused"]
-            alg_bytes = sum(BYTES[("batched", c)][u] * prof[c][u]
-                            for c in ("forward", "reverse") for u in BYTES[("batched", c)])
-            kernel_name = "k_batch_fused"
+            alg_bytes = sum(BYTES[("plain", c)][u] * prof[c][u]
+                            for c in ("forward", "reverse") for u in BYTES[("plain", c)])
+            kernel_name = "k_source"
         else:
             cls = max(("forward", "reverse"), key=lambda c: prof[c]["ms"])
             pc = prof[cls]

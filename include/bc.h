@@ -117,12 +117,12 @@ typedef struct bc_options {
 
 /* bc_options.level_loop.  HOST: the host launches every level step as
  * grid-wide kernels and polls the depth.  DEVICE: one workgroup runs a whole
- * batch (every level, with workgroup barriers) and all batches of the call go
- * in one launch: for small graphs, where launch and polling costs dominate,
- * or many batches.  AUTO picks the loop with the lower estimated time for the
- * call's batch count (a batch on one compute unit against a batch across the
- * device; e.g. DEVICE from about 6 batches at 53K arcs, 27 at 425K, 87 at
- * 1.8M).  A graph in extended range always takes HOST (or GRAPH).  GRAPH:
+ * source (every level, with workgroup barriers, the source's values in LDS)
+ * and all sources of the call go in one launch: for small graphs, where launch
+ * and polling costs dominate.  A source's values must fit a compute unit's
+ * LDS: graphs of more than 20,415 vertices take HOST.  AUTO picks the loop
+ * with the lower estimated time for the call's source count.  A graph in
+ * extended range always takes HOST (or GRAPH).  GRAPH:
  * the HOST loop with each chunk of level steps (the levels between two depth
  * polls, forward and reverse) captured once per workspace as a HIP graph and
  * replayed for every batch (the kernels read the chunk's base level from the
@@ -233,20 +233,15 @@ bc_status bc_run_multi(bc_graph_t g, const int32_t *sources, const int32_t *req_
 
 /*
  * BC of several graphs in one call (Section "Background", ComputeBC, on each
- * graph): graph i from its ks[i] sources into bc_outs_dev[i].  The 64-source
- * batches of the graphs that join go in one device-resident launch, one
- * workgroup per batch (two launches when some graphs keep double rows), so
- * many small graphs of uneven size share a launch; the others run after it on
- * the host-driven loop.  level_loop: BC_LOOP_DEVICE, every graph joins;
- * BC_LOOP_HOST, none does; BC_LOOP_AUTO, the graphs with the shortest batches
- * join, as many as minimise the estimated time of the launch (its slowest
- * batch) plus the host-loop runs of the rest (the cost model of
- * BC_LOOP_AUTO).  Each graph's result is bit-identical to bc_run_async on that
- * graph with BC_MODE_BATCHED, batch_width 64 and the loop reported in
- * loops[i]; a graph that joins but cannot stay (extended range, more batches
- * than its device-loop pool holds at once) or whose batches call for a rerun
- * (double rows, a longer level array) runs on its own afterwards, as such a
- * call would.
+ * graph): graph i from its ks[i] sources into bc_outs_dev[i].  The sources of
+ * the graphs that join go in one launch, one workgroup per source (a second
+ * launch for directed graphs), so many small graphs of uneven size share it;
+ * the others run after it on the host-driven loop.  level_loop:
+ * BC_LOOP_DEVICE, every graph small enough for that loop joins; BC_LOOP_HOST,
+ * none does; BC_LOOP_AUTO, the graphs that would take it on their own join.
+ * Each graph's result is bit-identical to bc_run_async on that graph with
+ * BC_MODE_BATCHED, batch_width 64 and the loop reported in loops[i]; a graph
+ * that needs the extended range runs on its own, as such a call would.
  *   graphs       [ngraphs] host array of distinct graphs on one device
  *   sources      [ngraphs] host array of host arrays: sources[i] holds ks[i]
  *                sources of graph i (NULL allowed where ks[i] == 0)
@@ -255,8 +250,8 @@ bc_status bc_run_multi(bc_graph_t g, const int32_t *sources, const int32_t *req_
  *                doubles, overwritten with BC (caller vertex order)
  *   level_loop   BC_LOOP_AUTO, BC_LOOP_HOST or BC_LOOP_DEVICE
  *   loops        NULL or [ngraphs] host: BC_LOOP_DEVICE or BC_LOOP_HOST per graph
- * Uses each graph's device-loop pool (as bc_run_async with BC_LOOP_DEVICE) and
- * allocates the launch's tables (device memory); waits on `stream`.  Errors:
+ * Uses each graph's workspaces (as bc_run_async with BC_LOOP_DEVICE); waits on
+ * `stream`.  Errors:
  * BC_ERR_INVALID_ARG (a NULL array or output, a graph given twice, graphs on
  * different devices, a source out of range, another level_loop), then as
  * bc_run_async.
@@ -290,21 +285,21 @@ bc_status bc_run_detail(bc_graph_t g, const int32_t *sources, int32_t k, const b
 
 /* Device bytes one run with k sources and the given options would take for its
  * workspaces (for admission control): one per concurrent part, or the
- * device-resident loop's per-batch pool, at the graph's current level-array
+ * device-resident loop's per-source scratch, at the graph's current level-array
  * estimate (a deeper graph grows it) and row width: while the graph's path
  * counts have fitted 32 bits, host-loop workspaces hold uint32 sigma rows, and
  * the run in which a count first passes 32 bits adds double rows (512 bytes
  * per vertex and 64 sources) to each part's workspace.  opt may be NULL. */
 bc_status bc_workspace_bytes(bc_graph_t g, int32_t k, const bc_options *opt, size_t *bytes);
 
-/* Free pooled workspaces that are idle (the one-source and batched pools'
- * idle entries, and the device-resident loop's pool when no run holds it).
+/* Free pooled workspaces that are idle (the idle entries of the one-source,
+ * batched and device-resident loops' pools).
  * Safe while other runs are in flight. */
 bc_status bc_trim_workspaces(bc_graph_t g);
 
 /* Device bytes the graph's BC workspace pools hold right now (idle or in use:
  * one-source and batched workspaces with their level arrays, the
- * device-resident loop's pool and tables), for admission control alongside
+ * device-resident loop's scratch), for admission control alongside
  * bc_workspace_bytes.  Excludes the graph itself (bc_graph_info), the SSSP and
  * PageRank workspaces, and a call's transient buffers. */
 bc_status bc_workspace_held(bc_graph_t g, size_t *bytes);
@@ -323,7 +318,7 @@ bc_status bc_workspace_held(bc_graph_t g, size_t *bytes);
  *   BC_PROF_PAGERANK the sum step of one bc_pagerank iteration (timing only;
  *                    its bytes follow from the graph's size)
  *   BC_PROF_FUSED    device-resident level loop: one launch runs whole
- *                    batches (its forward and reverse work counters are
+ *                    sources (its forward and reverse work counters are
  *                    added to FORWARD and REVERSE, which then show no launches)
  * owners = vertices processed (for COMPACT: vertices queued), arcs = adjacency
  * entries read, hits = parent arcs (FORWARD) or child arcs (REVERSE).
@@ -417,7 +412,7 @@ bc_status bc_autotune(bc_graph_t g, const int32_t *sources, int32_t k, void *str
  * or 8 and 128 for a graph of fewer than 8192 groups of 64 vertices (fewer
  * than 524,225 vertices), which has too few group items to fill the device.
  * The host-driven level loop uses them; the device-resident loop (one
- * workgroup per batch) always works on 64 and 512.
+ * workgroup per source) has no work items.
  *   group_cut  >= 1
  *   chunk      a multiple of 64 in [64, 4096], >= group_cut
  * Frees the graph's idle pooled batched workspaces (their partial rows follow

@@ -212,7 +212,7 @@ def bc_run_multi(g: int, requests, outs, stream=None) -> None:
 
 
 def bc_run_graphs(graphs, sources, outs, level_loop: int = BC_LOOP_AUTO, stream=None) -> list:
-    """BC of several graphs in one call (the batches of the graphs that join in
+    """BC of several graphs in one call (the sources of the graphs that join in
     one device-resident launch): graphs are Graph objects or handles,
     sources[i] the source array of graph i, outs[i] a float64 device tensor of
     n_i entries.  Returns the loop each graph ran on (BC_LOOP_DEVICE or

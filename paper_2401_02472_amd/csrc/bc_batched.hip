@@ -1365,106 +1365,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_finalize(BatchDev d, int32_t L
         finalize_level<N, H>(half_view<H>(d, H - 1), L, leaf, wave, gridDim.x * kWavesPerBlock);
 }
 
-// ---- device-resident level loop (small graphs) -----------------------------
-
-// One workgroup runs one whole batch: clear, seed, every forward level, every
-// reverse level and the completion, with a workgroup barrier between steps
-// (the waves of a workgroup share one compute unit and its L1, so the barrier
-// orders their global-memory accesses).  A call's batches run as the
-// workgroups of one launch.  The per-wave step code is the one the grid-wide
-// kernels run, inlined here as there: no kernel of this library makes calls
-// (with the steps as out-of-line calls, this kernel's dependency sums came
-// out wrong on gfx950, varying from run to run, while the level masks and
-// path counts stayed exact).  ctrl of the batch receives the depth and the flags
-// (truncation: the host runs the call again with a longer level array).  No
-// extended range and no 128-source batches here: the host runs those on its
-// own loop.
-constexpr int kFusedBlock = 1024;
-constexpr int kFusedWaves = kFusedBlock / kWave;
-
-template <bool N>
-__global__ __launch_bounds__(kFusedBlock) void k_batch_fused(const BatchDev *devs,
-                                                             const int32_t *lanes,
-                                                             const int2 *batches) {
-    const BatchDev &d = devs[blockIdx.x];
-    const int2 bt = batches[blockIdx.x];  // (first lane in `lanes`, lane count)
-    const int t = threadIdx.x;
-    const int lane = lane_id();
-    const int32_t wave = t / kWave;
-    __shared__ uint32_t s_found;
-    // clear
-    for (int32_t i = t; i < d.n; i += kFusedBlock) {
-        d.vis[i] = 0ull;
-        d.F[i] = 0ull;
-        if (d.nseg == 0) d.bc[i] = 0.0;
-    }
-    for (int32_t i = t; i < d.multi_end; i += kFusedBlock) d.reach[i] = 0ull;
-    if (t < kCtlInts) d.ctrl[t] = 0;
-    __syncthreads();
-    // seed
-    const int32_t nl = bt.y;
-    if (wave == 0 && lane < nl) {
-        const int32_t s = lanes[bt.x + lane];
-        atomicOr((unsigned long long *)&d.vis[s], 1ull << lane);
-        atomicOr((unsigned long long *)&d.F[s], 1ull << lane);
-        SigRows<N>::rows(d)[(size_t)s * kWave + lane] = 1;
-    }
-    __syncthreads();
-    const uint64_t full = nl >= 64 ? ~0ull : ((1ull << nl) - 1ull);
-    const uint32_t items = d.items;         // reverse (arcs out of a vertex)
-    const uint32_t items_in = d.items_in;   // forward (arcs into a vertex)
-    const uint32_t groups = (uint32_t)((d.n - d.big_end + kWave - 1) / kWave);
-    // forward
-    int32_t deepest = 0;
-    bool trunc = false;
-    Work wkf, wkr;
-    for (int32_t L = 0;; ++L) {
-        if (L + 1 >= d.lcap) {  // level L+1 does not fit
-            trunc = true;
-            break;
-        }
-        if (t == 0) s_found = 0;
-        Front fr;
-        for (uint32_t it = wave; it < items_in + groups; it += kFusedWaves) {
-            if (it < items_in) fwd_chunk<N, 1>(d, L, it, full, 1.0, wkf, fr);
-            else fwd_group<N, 1>(d, L, d.big_end + (int32_t)(it - items_in) * kWave, nullptr, 0,
-                              full, 1.0, wkf, fr);
-        }
-        __syncthreads();
-        finish_split<N, 1>(d, L, wave, kFusedWaves, 1.0, fr);
-        uint32_t c = fr.cnt;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
-        if (lane == 0 && c) atomicAdd(&s_found, c);
-        __syncthreads();
-        const uint32_t found = s_found;
-        __syncthreads();  // s_found is reset by the next iteration
-        if (found == 0) break;
-        deepest = L + 1;
-    }
-    if (t == 0) {
-        d.ctrl[kCtlDeepest] = deepest;
-        if (trunc) d.ctrl[kCtlTrunc] = 1;
-    }
-    if (trunc) return;
-    // reverse
-    for (int32_t L = deepest; L >= 1; --L) {
-        if (L != deepest) {
-            for (uint32_t it = wave; it < items + groups; it += kFusedWaves) {
-                if (it < items) bwd_chunk<N, 1>(d, L, it, 1.0, wkr);
-                else bwd_group<N, 1>(d, L, d.big_end + (int32_t)(it - items) * kWave, 1.0, wkr);
-            }
-            __syncthreads();
-        }
-        finalize_level<N, 1>(d, L, L == deepest ? 1 : 0, wave, kFusedWaves);
-        __syncthreads();
-    }
-    if (d.stats) {
-        report_work(d.stats, 0, 12, wkf);
-        report_work(d.stats, 6, 13, wkr);
-    }
-}
-
 // ---- batch set-up and export ------------------------------------------------
 
 // vis = 0 and F_0 = 0 everywhere; the split vertices' reach masks cleared.
@@ -1653,14 +1553,6 @@ hipError_t batch_level_advance(const BatchDev &d, int32_t delta, hipStream_t str
 
 hipError_t batch_level_from_deepest(const BatchDev &d, hipStream_t stream) {
     hipLaunchKernelGGL(k_level_from_deepest, dim3(1), dim3(1), 0, stream, d.ctrl);
-    return hipGetLastError();
-}
-
-hipError_t batch_fused(const BatchDev *devs_dev, int32_t nbatches, bool narrow,
-                       const int32_t *lanes_dev, const int2 *batches_dev, hipStream_t stream) {
-    if (nbatches <= 0) return hipSuccess;
-    hipLaunchKernelGGL(narrow ? k_batch_fused<true> : k_batch_fused<false>, dim3(nbatches),
-                       dim3(kFusedBlock), 0, stream, devs_dev, lanes_dev, batches_dev);
     return hipGetLastError();
 }
 

@@ -8,9 +8,9 @@ using namespace bcx;
 
 namespace bcx {
 
-// A plain run whose counts overflowed double: the graph switches to the
-// batched path's extended range for this and every later call.
-void plain_overflowed(bc_graph_s *g) {
+// A run whose counts overflowed double: the graph switches to the batched
+// path's extended range for this and every later call.
+void range_exceeded(bc_graph_s *g) {
     g->sigma_wide.store(true);
     g->sigma_ext.store(true);
 }
@@ -21,17 +21,21 @@ bool use_batched(const bc_graph_s *g, const bc_options *opt, int32_t k) {
     const int32_t mode = opt ? opt->mode : BC_MODE_AUTO;
     if (mode == BC_MODE_BATCHED) return true;
     if (mode == BC_MODE_PLAIN) return false;
-    return k >= g->tuned_min_batched.load();
+    if (k >= g->tuned_min_batched.load()) return true;
+    // few sources: a workgroup per source (a batched loop) against the
+    // one-source path, which spreads each source over the device
+    return use_source(g, opt ? opt->level_loop : BC_LOOP_AUTO, k, batch_width_of(g, opt, k)) &&
+           source_beats_plain(g, k);
 }
 
 int32_t batch_width_of(const bc_graph_s *g, const bc_options *opt, int32_t k) {
     if (opt && opt->batch_width > 0) return opt->batch_width;
     const int32_t w = g->tuned_width.load();
-    // a tuned width above 64 was timed on a sample that runs on the host
-    // loop; where 64-wide batches of the whole run take the device-resident
-    // loop (one lane word per vertex), those are the faster choice
+    // a tuned width above 64 was timed on a sample that ran on the host loop;
+    // where the whole run takes a workgroup per source, that is the faster
+    // choice
     const int32_t loop = opt ? opt->level_loop : BC_LOOP_AUTO;
-    if (w > kWave && k > 0 && use_fused(g, loop, (k + kWave - 1) / kWave, kWave)) return kWave;
+    if (w > kWave && k > 0 && use_source(g, loop, k, kWave)) return kWave;
     return w;
 }
 
@@ -91,7 +95,7 @@ bc_status bc_run_async(bc_graph_t g, const int32_t *sources, int32_t k, double *
     if (!use_batched(g, opt, k)) {
         st = plain_run(g, sources, k, bc_out_dev, opt, (hipStream_t)stream, nullptr, nullptr);
         if (st != BC_ERR_RANGE) return st;
-        plain_overflowed(g);
+        range_exceeded(g);
     }
     return batched_run(g, sources, k, bc_out_dev, batch_width_of(g, opt, k), sparse_div_of(g, opt),
                        opt ? opt->concurrency : 0, opt ? opt->level_loop : 0,
@@ -109,7 +113,7 @@ bc_status bc_run(bc_graph_t g, const int32_t *sources, int32_t k, double *bc_out
     st = BC_ERR_RANGE;
     if (!use_batched(g, nullptr, k)) {
         st = plain_run(g, sources, k, d_bc, nullptr, nullptr, nullptr, nullptr);
-        if (st == BC_ERR_RANGE) plain_overflowed(g);
+        if (st == BC_ERR_RANGE) range_exceeded(g);
     }
     if (st == BC_ERR_RANGE)
         st = batched_run(g, sources, k, d_bc, batch_width_of(g, nullptr, k), sparse_div_of(g, nullptr),
@@ -162,7 +166,7 @@ bc_status bc_run_detail(bc_graph_t g, const int32_t *sources, int32_t k, const b
     if (!batched) {
         st = plain_run(g, sources, k, d_bc, opt, nullptr, (dist || sigma) ? exp.data() : nullptr,
                        &tmp.t);
-        if (st == BC_ERR_RANGE) plain_overflowed(g);
+        if (st == BC_ERR_RANGE) range_exceeded(g);
     }
     if (st == BC_ERR_RANGE)
         st = batched_run(g, sources, k, d_bc, batch_width_of(g, opt, k), sparse_div_of(g, opt),
@@ -270,12 +274,8 @@ bc_status bc_workspace_bytes(bc_graph_t g, int32_t k, const bc_options *opt, siz
     const int32_t nb = (k + width - 1) / width;
     const int32_t H = width > kWave ? 2 : 1;
     const int32_t lcap = std::max(16, g->batch_depth_hint.load() + 8);
-    if (use_fused(g, opt ? opt->level_loop : 0, nb, width)) {
-        // the device-loop pool: per-batch workspaces, BC arrays and control words
-        const int32_t cap = fused_cap(g, nb, lcap);
-        const size_t n = (size_t)std::max<int32_t>(g->n, 1);
-        *bytes = (size_t)cap * (fused_batch_bytes(g, lcap) + n * sizeof(double) +
-                                kCtlInts * sizeof(int32_t)) + n * sizeof(double);
+    if (use_source(g, opt ? opt->level_loop : 0, k, width)) {
+        *bytes = source_bytes(g, k);
     } else {
         // one workspace per concurrent part
         const int32_t parts = parts_of(g, opt ? opt->concurrency : 0, nb, H);
@@ -306,14 +306,7 @@ bc_status bc_workspace_held(bc_graph_t g, size_t *bytes) {
         for (const PlainWS *ws : g->plain_pool) b += ws->bytes + ws->trunc_cap * sizeof(int32_t);
         for (const BatchWS *ws : g->batch_pool)
             b += ws->bytes + (ws->lcap ? batch_level_bytes(g, ws->lcap, ws->H) : 0) + ws->src_cap;
-    }
-    {
-        std::lock_guard<std::mutex> lk(g->fused_mu);
-        const auto &f = g->fused;
-        if (f.block)
-            b += f.bytes + (size_t)f.cap * (sizeof(BatchDev) + sizeof(int2));
-        if (f.d_total) b += (size_t)std::max<int32_t>(g->n, 1) * sizeof(double);
-        b += f.lanes_cap;
+        for (const SourceWS *ws : g->source_pool) b += ws->bytes;
     }
     *bytes = b;
     return BC_OK;
@@ -322,13 +315,9 @@ bc_status bc_workspace_held(bc_graph_t g, size_t *bytes) {
 bc_status bc_trim_workspaces(bc_graph_t g) {
     if (!g) return BC_ERR_INVALID_ARG;
     DeviceGuard dg(g->device);
-    {
-        // the device-loop pool, unless a run holds it
-        std::unique_lock<std::mutex> lk(g->fused_mu, std::try_to_lock);
-        if (lk.owns_lock()) fused_release(g);
-    }
     std::vector<PlainWS *> idle;
     std::vector<BatchWS *> idle_b;
+    std::vector<SourceWS *> idle_s;
     {
         std::lock_guard<std::mutex> lk(g->mu);
         std::vector<PlainWS *> keep;
@@ -337,9 +326,13 @@ bc_status bc_trim_workspaces(bc_graph_t g) {
         std::vector<BatchWS *> keep_b;
         for (BatchWS *ws : g->batch_pool) (ws->busy ? keep_b : idle_b).push_back(ws);
         g->batch_pool.swap(keep_b);
+        std::vector<SourceWS *> keep_s;
+        for (SourceWS *ws : g->source_pool) (ws->busy ? keep_s : idle_s).push_back(ws);
+        g->source_pool.swap(keep_s);
     }
     for (PlainWS *ws : idle) plain_ws_destroy(ws);
     for (BatchWS *ws : idle_b) batch_ws_destroy(ws);
+    for (SourceWS *ws : idle_s) source_ws_destroy(ws);
     return BC_OK;
 }
 
@@ -348,7 +341,7 @@ bc_status bc_trim_workspaces(bc_graph_t g) {
 // with part of a wave inactive, over every kernel file, since the last call.
 unsigned int bc_debug_exec_partial(void) {
     return exec_partial_batched() + exec_partial_plain() + exec_partial_sssp() +
-           exec_partial_pagerank();
+           exec_partial_pagerank() + exec_partial_source();
 }
 #endif
 

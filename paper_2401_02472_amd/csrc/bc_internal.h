@@ -10,6 +10,7 @@
 namespace bcx {
 
 constexpr int kWave = 64;             // CDNA wavefront width
+constexpr int kCus = 256;             // compute units of an MI355X
 constexpr int kBlock = 256;           // threads per workgroup for the level kernels
 constexpr int kWavesPerBlock = kBlock / kWave;
 
@@ -209,6 +210,7 @@ unsigned int exec_partial_batched();
 unsigned int exec_partial_plain();
 unsigned int exec_partial_sssp();
 unsigned int exec_partial_pagerank();
+unsigned int exec_partial_source();
 #endif
 
 // Launchers (bc_batched.hip).  All are asynchronous on `stream`.
@@ -231,13 +233,58 @@ hipError_t batch_finalize_rel(const BatchDev &d, int32_t level_rel, hipStream_t 
 hipError_t batch_level_advance(const BatchDev &d, int32_t delta, hipStream_t stream);
 hipError_t batch_level_from_deepest(const BatchDev &d, hipStream_t stream);
 // dist [nlanes][n] (int32) and sigma [nlanes][n] of the batch, internal order.
-// Every batch of a call in one launch, one workgroup per batch (graphs small
-// enough for one compute unit per batch); devs_dev[b] is batch b's workspace,
-// batches_dev[b] = (first lane in lanes_dev, lane count).
-hipError_t batch_fused(const BatchDev *devs_dev, int32_t nbatches, bool narrow,
-                       const int32_t *lanes_dev, const int2 *batches_dev, hipStream_t stream);
 hipError_t batch_export(const BatchDev &d, int32_t deepest, int32_t nlanes, int32_t *dist,
                         double *sigma, hipStream_t stream);
+
+// One-workgroup-per-source Brandes (bc_source.hip).
+constexpr int kSrcClasses = 4;   // degree classes: > 512 arcs, 65 .. 512, 9 .. 64, up to 8
+// LDS a workgroup may take (160 KB, less the kernel's own few words)
+constexpr size_t kSrcLdsBytes = 160 * 1024 - 512;
+
+// Spare ids (zeros) past the end of a graph's arc arrays: loads of several ids
+// may pass the last arc.
+constexpr int kArcPad = 4;
+
+// A graph as the source kernel sees it: internal ids are degree-descending,
+// so class c is the id range [cls[c], cls[c + 1]).
+struct SourceGraph {
+    int32_t n;
+    int32_t cls[kSrcClasses + 1];
+    const int32_t *row_ptr, *col_idx;        // arcs out
+    const int32_t *row_ptr_in, *col_idx_in;  // arcs in (the same arrays when undirected)
+    const int32_t *perm, *iperm;
+};
+
+// The work of one workgroup: `count` sources of one request, their
+// dependencies added to `row` (internal order).
+struct SourceUnit {
+    int32_t graph, first, count;
+    double *row;       // [n]
+    int32_t *q;        // [n]
+    double *sig;       // [n]
+    uint32_t *lvl;     // [n + 2][kSrcClasses] level starts in the queues
+    double *out;       // NULL, or the request's BC (caller order) written by this unit
+    int32_t *dist;     // exports (caller order), NULL unless asked for:
+    double *sigma;     // row export_row[i] for the unit's source i
+    const int32_t *export_row;
+};
+
+// One request's BC from its units' rows.
+struct SourceSum {
+    int32_t n, units;
+    size_t stride;             // doubles between the units' rows
+    const double *row;
+    const int32_t *iperm;
+    double *out;
+};
+
+// LDS of a workgroup on a graph of n vertices.
+size_t source_lds_bytes(int32_t n);
+// range[u.graph] is set to 1 where a count passes double's range.
+hipError_t source_run(const SourceUnit *units, int32_t nunits, const SourceGraph *graphs,
+                      const int32_t *sources, bool directed, size_t lds, int32_t *range,
+                      unsigned long long *stats, hipStream_t stream);
+hipError_t source_sum(const SourceSum *sums, int32_t nsums, int32_t max_n, hipStream_t stream);
 
 // Device view of a single-source shortest-path run (bc_sssp.hip): the graph's
 // out-arcs with their weights (NULL: every arc weighs 1), the same chunk items

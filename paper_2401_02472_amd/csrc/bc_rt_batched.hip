@@ -1,6 +1,6 @@
 // Host side of the batched path: batch workspaces, batch composition
-// (landmark order), the host-driven level loop, the device-resident loop's
-// workspace pool, concurrent parts and multi-request batching.
+// (landmark order), the host-driven level loop, concurrent parts and
+// multi-request batching.
 #include "bc_runtime.h"
 
 namespace bcx {
@@ -523,495 +523,55 @@ bc_status run_batch_plan(bc_graph_s *g, const std::vector<int32_t> &s_int,
     return range ? BC_ERR_RANGE : BC_OK;
 }
 
-// ---- device-resident level loop ----------------------------------------------
-
-// Bytes of one batch's workspace in the fused pool (vis, sigma / coef rows,
-// split-vertex rows, partial rows, the level array).
-size_t fused_batch_bytes(const bc_graph_s *g, int32_t lcap) {
-    const size_t n = (size_t)std::max<int32_t>(g->n, 1);
-    const bc_graph_s::BcItems t = base_items(g);
-    const size_t multi = (size_t)std::max(t.multi_end, 1);
-    return align_up(n * sizeof(uint64_t)) + 2 * align_up(n * kWave * sizeof(double)) +
-           align_up(multi * sizeof(uint64_t)) + align_up(partial_rows(t) * kWave * sizeof(double)) +
-           align_up((size_t)lcap * n * sizeof(uint64_t));
-}
-
-// The batch workspaces of the pool (not the run's lane and segment tables).
-void fused_release_pool(bc_graph_s *g) {
-    auto &f = g->fused;
-    if (f.block) (void)hipFree(f.block);
-    if (f.d_devs) (void)hipFree(f.d_devs);
-    if (f.h_ctrl) (void)hipHostFree(f.h_ctrl);
-    if (f.d_batches) (void)hipFree(f.d_batches);
-    f.block = nullptr;
-    f.d_devs = nullptr;
-    f.h_ctrl = nullptr;
-    f.d_batches = nullptr;
-    f.d_ctrl = nullptr;
-    f.d_bc = nullptr;
-    f.bytes = 0;
-    f.cap = f.lcap = 0;
-    f.h_devs.clear();
-}
-
-void fused_release(bc_graph_s *g) {
-    fused_release_pool(g);
-    auto &f = g->fused;
-    if (f.d_lanes) (void)hipFree(f.d_lanes);
-    if (f.d_total) (void)hipFree(f.d_total);
-    if (f.d_stats) (void)hipFree(f.d_stats);
-    f.d_lanes = nullptr;
-    f.d_total = nullptr;
-    f.d_stats = nullptr;
-    f.lanes_cap = 0;
-}
-
-// Batches per launch that fit the pool budget with `lcap` levels each.
-constexpr size_t kFusedBudget = (size_t)4 << 30;
-int32_t fused_cap(const bc_graph_s *g, int32_t nbatches, int32_t lcap) {
-    const size_t per = fused_batch_bytes(g, lcap);
-    return (int32_t)std::max<size_t>(1, std::min<size_t>((size_t)std::max(nbatches, 1),
-                                                         kFusedBudget / per));
-}
-
-// Pool for `cap` batches with `lcap` levels each (caller holds fused_mu); an
-// existing pool at least that large is kept.
-bc_status fused_reserve(bc_graph_s *g, int32_t cap, int32_t lcap) {
-    auto &f = g->fused;
-    if (f.block && f.cap >= cap && f.lcap >= lcap) return BC_OK;
-    fused_release_pool(g);
-    const size_t n = (size_t)std::max<int32_t>(g->n, 1);
-    const size_t per = fused_batch_bytes(g, lcap);
-    const size_t head = align_up((size_t)cap * kCtlInts * sizeof(int32_t)) +
-                        align_up((size_t)cap * n * sizeof(double));
-    f.bytes = head + (size_t)cap * per;
-    hipError_t e = hipMalloc(&f.block, f.bytes);
-    if (e == hipSuccess) e = hipMalloc(&f.d_devs, (size_t)cap * sizeof(BatchDev));
-    if (e == hipSuccess) e = hipMalloc(&f.d_batches, (size_t)cap * sizeof(int2));
-    if (e == hipSuccess)
-        e = hipHostMalloc((void **)&f.h_ctrl, (size_t)cap * kCtlInts * sizeof(int32_t),
-                          hipHostMallocDefault);
-    if (e != hipSuccess) {
-        fused_release(g);
-        return from_hip(e);
-    }
-    f.cap = cap;
-    f.lcap = lcap;
-    const bc_graph_s::BcItems items = base_items(g);
-    char *p = (char *)f.block;
-    auto take = [&](size_t bytes) {
-        char *r = p;
-        p += align_up(bytes);
-        return (void *)r;
-    };
-    f.d_ctrl = (int32_t *)take((size_t)cap * kCtlInts * sizeof(int32_t));
-    f.d_bc = (double *)take((size_t)cap * n * sizeof(double));
-    f.h_devs.assign((size_t)cap, BatchDev{});
-    for (int32_t b = 0; b < cap; ++b) {
-        BatchDev &d = f.h_devs[(size_t)b];
-        d.n = g->n;
-        d.H = 1;
-        d.row_ptr = g->d_row_ptr;
-        d.col_idx = g->d_col_idx;
-        set_items(items, d);
-        d.row_ptr_in = g->d_row_ptr_in;
-        d.col_idx_in = g->d_col_idx_in;
-        d.iperm = g->d_iperm;
-        d.nnz = g->nnz;
-        d.lcap = lcap;
-        d.ctrl = f.d_ctrl + (size_t)b * kCtlInts;
-        d.bc = f.d_bc + (size_t)b * n;
-        d.vis = (uint64_t *)take(n * sizeof(uint64_t));
-        d.sigma = (double *)take(n * kWave * sizeof(double));
-        d.sigma32 = reinterpret_cast<uint32_t *>(d.sigma);
-        d.coef = (double *)take(n * kWave * sizeof(double));
-        d.reach = (uint64_t *)take((size_t)std::max(items.multi_end, 1) * sizeof(uint64_t));
-        d.partial = (double *)take(partial_rows(items) * kWave * sizeof(double));
-        d.F = (uint64_t *)take((size_t)lcap * n * sizeof(uint64_t));
-    }
-    return BC_OK;
-}
-
-// The whole batch plan with the device-resident level loop: up to `cap`
-// batches per launch (one workgroup each).  Without segments, BC (caller
-// order) = the batches' BC added in batch order; with segments, each batch
-// adds its lanes' dependencies to its requests' outputs (requests of at most
-// 64 sources only, so no two batches of a launch share an output).
-bc_status fused_run(bc_graph_s *g, const std::vector<int32_t> &s_int,
-                    const std::vector<BatchPlan> &plan, const std::vector<int32_t> &seg_start,
-                    const std::vector<double *> &seg_out, double *bc_out, hipStream_t stream,
-                    const int32_t *export_row, int32_t *dist, double *sigma) {
-    std::lock_guard<std::mutex> lk(g->fused_mu);
-    const int32_t nb = (int32_t)plan.size();
-    const size_t n = (size_t)g->n;
-    auto &f = g->fused;
-    const bool prof = g->profiling.load() != 0;
-    const int32_t lcap = std::max(16, g->batch_depth_hint.load() + 8);
-    bc_status st = fused_reserve(g, fused_cap(g, nb, lcap), lcap);
-    if (st != BC_OK) return st;
-    // the running BC total outlives pool regrowth
-    if (bc_out && !f.d_total) BC_TRY_HIP(hipMalloc(&f.d_total, std::max<size_t>(n, 1) * sizeof(double)));
-    // lanes and segment tables on the device
-    const size_t k = s_int.size();
-    const size_t seg_ints = seg_start.size(), seg_ptrs = seg_out.size();
-    const size_t need = k * sizeof(int32_t) + seg_ints * sizeof(int32_t) +
-                        seg_ptrs * sizeof(double *) + 64;
-    if (need > f.lanes_cap) {
-        if (f.d_lanes) (void)hipFree(f.d_lanes);
-        f.d_lanes = nullptr;
-        f.lanes_cap = 0;
-        BC_TRY_HIP(hipMalloc(&f.d_lanes, need));
-        f.lanes_cap = need;
-    }
-    int32_t *d_seg_start = f.d_lanes + k;
-    double **d_seg_out = (double **)(((uintptr_t)(d_seg_start + seg_ints) + 15) & ~(uintptr_t)15);
-    hipError_t e = hipSuccess;
-    if (k) e = hipMemcpyAsync(f.d_lanes, s_int.data(), k * sizeof(int32_t), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && seg_ints)
-        e = hipMemcpyAsync(d_seg_start, seg_start.data(), seg_ints * sizeof(int32_t),
-                           hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && seg_ptrs)
-        e = hipMemcpyAsync(d_seg_out, seg_out.data(), seg_ptrs * sizeof(double *),
-                           hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) return from_hip(e);
-    int32_t *x_dist = nullptr;
-    double *x_sigma = nullptr;
-    struct Tmp {
-        int32_t *&a;
-        double *&b;
-        ~Tmp() {
-            if (a) (void)hipFree(a);
-            if (b) (void)hipFree(b);
-        }
-    } tmp_guard{x_dist, x_sigma};
-    if (dist) BC_TRY_HIP(hipMalloc(&x_dist, (size_t)kWave * n * sizeof(int32_t)));
-    if (sigma) BC_TRY_HIP(hipMalloc(&x_sigma, (size_t)kWave * n * sizeof(double)));
-    LaunchTimer timer;
-    timer.on = prof;
-    if (prof) {
-        if (!f.d_stats) BC_TRY_HIP(hipMalloc(&f.d_stats, kStatWords * sizeof(unsigned long long)));
-        BC_TRY_HIP(hipMemsetAsync(f.d_stats, 0, kStatWords * sizeof(unsigned long long), stream));
-    }
-    bool range = false;
-    int32_t run_depth = 0;
-    int64_t level_steps = 0;  // forward and reverse, over the batches
-    std::vector<int2> bt;
-    for (int32_t b0 = 0; b0 < nb;) {
-        const int32_t m = std::min(f.cap, nb - b0);
-        bt.resize((size_t)std::max(m, 1));
-        const bool narrow = !g->sigma_wide.load();
-        for (int32_t i = 0; i < m; ++i) {
-            const BatchPlan &bp = plan[(size_t)(b0 + i)];
-            BatchDev &d = f.h_devs[(size_t)i];
-            d.narrow = narrow ? 1 : 0;
-            d.stats = prof ? f.d_stats : nullptr;
-            d.nseg = bp.nseg;
-            d.seg_start = bp.nseg ? d_seg_start + bp.seg_first : nullptr;
-            d.seg_out = bp.nseg ? d_seg_out + (bp.seg_first - (b0 + i)) : nullptr;
-            bt[(size_t)i] = make_int2(bp.first, bp.nlanes);
-        }
-        e = hipMemcpyAsync(f.d_devs, f.h_devs.data(), (size_t)m * sizeof(BatchDev),
-                           hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(f.d_batches, bt.data(), (size_t)m * sizeof(int2),
-                               hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess) e = timer.begin(BC_PROF_FUSED, stream);
-        if (e == hipSuccess) e = batch_fused(f.d_devs, m, narrow, f.d_lanes, f.d_batches, stream);
-        if (e == hipSuccess) e = timer.end(stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(f.h_ctrl, f.d_ctrl, (size_t)m * kCtlInts * sizeof(int32_t),
-                               hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
-        if (e != hipSuccess) break;
-        bool trunc = false, wide = false, over = false;
-        for (int32_t i = 0; i < m; ++i) {
-            const int32_t *c = f.h_ctrl + (size_t)i * kCtlInts;
-            trunc |= c[kCtlTrunc] != 0;
-            wide |= c[kCtlNarrow] != 0;
-            over |= c[kCtlRange] != 0;
-        }
-        if (wide) {  // a path count needs double rows: run these batches again
-            g->sigma_wide.store(true);
-            continue;
-        }
-        if (over) {  // beyond double: the caller runs the call again level-scaled
-            g->sigma_ext.store(true);
-            timer.destroy();
-            return BC_ERR_RANGE;
-        }
-        if (trunc) {  // a batch ran deeper than the level array: grow it, run again
-            const int32_t l2 = f.lcap * 2;
-            fused_release_pool(g);  // the longer arrays may hold fewer batches
-            st = fused_reserve(g, fused_cap(g, nb - b0, l2), l2);
-            if (st != BC_OK) return st;
-            continue;
-        }
-        for (int32_t i = 0; i < m; ++i) {
-            const int32_t *c = f.h_ctrl + (size_t)i * kCtlInts;
-            range |= c[kCtlRange] != 0;
-            run_depth = std::max(run_depth, c[kCtlDeepest]);
-            level_steps += 2 * (int64_t)c[kCtlDeepest] + 1;
-        }
-        if (export_row && (dist || sigma)) {
-            for (int32_t i = 0; i < m && e == hipSuccess; ++i) {
-                const BatchPlan &bp = plan[(size_t)(b0 + i)];
-                const BatchDev &d = f.h_devs[(size_t)i];
-                e = batch_export(d, f.h_ctrl[(size_t)i * kCtlInts + kCtlDeepest], bp.nlanes, x_dist,
-                                 x_sigma, stream);
-                for (int32_t s2 = 0; s2 < bp.nlanes && e == hipSuccess; ++s2) {
-                    const size_t row = (size_t)export_row[bp.first + s2] * n;
-                    if (dist) e = gather_i32(g->n, g->d_perm, x_dist + (size_t)s2 * n, dist + row, stream);
-                    if (e == hipSuccess && sigma)
-                        e = gather_f64(g->n, g->d_perm, x_sigma + (size_t)s2 * n, sigma + row, stream);
-                }
-            }
-        }
-        if (e == hipSuccess && bc_out) e = sum_parts(g->n, f.d_bc, m, f.d_total, stream, b0 > 0);
-        if (e != hipSuccess) break;
-        b0 += m;
-    }
-    if (e == hipSuccess && bc_out) {
-        if (nb == 0) e = hipMemsetAsync(bc_out, 0, n * sizeof(double), stream);
-        else e = gather_f64(g->n, g->d_perm, f.d_total, bc_out, stream);
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) {
-        timer.destroy();
-        return from_hip(e);
-    }
-    if (nb > 0) g->batch_depth_hint.store(run_depth);
-    if (prof) accumulate_profile(g, timer, f.d_stats, level_steps);
-    timer.destroy();
-    return range ? BC_ERR_RANGE : BC_OK;
-}
-
-bc_status make_plan(bc_graph_s *g, const int32_t *sources, int32_t k, int32_t width,
-                    std::vector<int32_t> &order, std::vector<int32_t> &s_int,
-                    std::vector<BatchPlan> &plan);
-
-// Several graphs' batches in one device-resident launch (one per row width):
-// each graph's plan is batched_run's at width 64 and each batch runs on its
-// graph's pool, so every graph's BC is bit-identical to its own device-loop
-// run.  A graph that cannot join (extended range, more batches than its pool
-// holds at once) or whose batches call for a rerun (wider rows, a longer
-// level array, counts past double's range) runs on its own afterwards, as
-// bc_run_async with the device-resident loop would run it.
+// Several graphs in one call: the sources of the graphs that join go in one
+// launch, a workgroup per source (one launch per kind of graph); every
+// graph's BC is made of the same units as its own run's, so it is
+// bit-identical to it.  A graph that cannot join (extended range, too large)
+// or whose counts pass double's range runs on its own afterwards.
 bc_status run_graphs(bc_graph_s *const *gs, int32_t ng, const int32_t *const *sources,
                      const int32_t *ks, double *const *outs, int32_t level_loop,
                      int32_t *loops, hipStream_t stream) {
-    // BC_LOOP_AUTO: the graphs that join are the prefix, by one batch's
-    // estimated device-loop time, that minimises the launch (its slowest
-    // batch, times the rounds of 256 batches: the batches run side by side,
-    // one workgroup each) plus the host-loop estimates of the graphs left out
-    // (the cost model of use_fused)
-    std::vector<char> join((size_t)ng, level_loop == BC_LOOP_HOST ? 0 : 1);
-    if (level_loop == BC_LOOP_AUTO) {
-        std::vector<int32_t> idx;
-        for (int32_t i = 0; i < ng; ++i)
-            if (gs[i]->n > 0 && ks[i] > 0) idx.push_back(i);
-        auto dev_t = [&](int32_t i) { return 2e-3 + 50e-9 * (double)gs[i]->nnz; };
-        auto host_t = [&](int32_t i) {
-            return std::ceil((double)ks[i] / kWave) * (0.8e-3 + 0.15e-9 * (double)gs[i]->nnz);
-        };
-        std::stable_sort(idx.begin(), idx.end(),
-                         [&](int32_t a, int32_t b) { return dev_t(a) < dev_t(b); });
-        double rest = 0.0;
-        for (int32_t i : idx) rest += host_t(i);
-        double best = rest;  // nothing joins
-        size_t best_j = 0;
-        double batches = 0.0;
-        for (size_t j = 0; j < idx.size(); ++j) {
-            rest -= host_t(idx[j]);
-            batches += std::ceil((double)ks[idx[j]] / kWave);
-            const double t = dev_t(idx[j]) * std::ceil(batches / 256.0) + rest;
-            if (t < best) {
-                best = t;
-                best_j = j + 1;
-            }
-        }
-        std::fill(join.begin(), join.end(), 0);
-        for (size_t j = 0; j < best_j; ++j) join[(size_t)idx[j]] = 1;
-    }
-    struct Part {
-        int32_t i = 0;                  // graph index
-        std::vector<int32_t> order, s_int;
-        std::vector<BatchPlan> plan;
-        int32_t lane0 = 0;              // first lane in the combined lane array
-        bool narrow = true;             // row width, read once for the call
-        bool alone = false;
-    };
-    std::vector<Part> parts;
-    std::vector<int32_t> alone;
-    bc_status st = BC_OK;
-    for (int32_t i = 0; i < ng && st == BC_OK; ++i) {
+    // the graphs whose own run would take a workgroup per source join
+    std::vector<char> join((size_t)ng, 0);
+    for (int32_t i = 0; i < ng; ++i) join[(size_t)i] = use_source(gs[i], level_loop, ks[i], kWave);
+    std::vector<SourceJob> jobs;
+    std::vector<int32_t> at, alone;
+    for (int32_t i = 0; i < ng; ++i) {
         bc_graph_s *g = gs[i];
         if (g->n == 0) continue;
-        const int32_t lcap = std::max(16, g->batch_depth_hint.load() + 8);
-        const int32_t nb = (ks[i] + kWave - 1) / kWave;
-        if (!join[(size_t)i] || ks[i] == 0 || g->sigma_ext.load() || fused_cap(g, nb, lcap) < nb) {
+        if (!join[(size_t)i]) {
             alone.push_back(i);
             continue;
         }
-        Part p;
-        p.i = i;
-        st = make_plan(g, sources[i], ks[i], kWave, p.order, p.s_int, p.plan);
-        parts.push_back(std::move(p));
+        SourceJob job;
+        job.g = g;
+        job.s_int.resize((size_t)ks[i]);
+        for (int32_t s = 0; s < ks[i]; ++s) job.s_int[(size_t)s] = g->h_perm[(size_t)sources[i][s]];
+        job.reqs.push_back({0, ks[i], outs[i]});
+        jobs.push_back(std::move(job));
+        at.push_back(i);
     }
+    std::vector<char> over;
+    const bc_status st = source_jobs(jobs, stream, over);
     if (st != BC_OK) return st;
-    // every pool of the launch held, locked in address order
-    std::vector<bc_graph_s *> locked;
-    for (const Part &p : parts) locked.push_back(gs[p.i]);
-    std::sort(locked.begin(), locked.end());
-    std::vector<std::unique_lock<std::mutex>> locks;
-    for (bc_graph_s *g : locked) locks.emplace_back(g->fused_mu);
-    int32_t lanes = 0, batches = 0;
-    for (Part &p : parts) {
-        bc_graph_s *g = gs[p.i];
-        const int32_t lcap = std::max(16, g->batch_depth_hint.load() + 8);
-        st = fused_reserve(g, (int32_t)p.plan.size(), lcap);
-        if (st == BC_OK && !g->fused.d_total)
-            st = from_hip(hipMalloc(&g->fused.d_total, (size_t)g->n * sizeof(double)));
-        if (st != BC_OK) return st;
-        p.lane0 = lanes;
-        p.narrow = !g->sigma_wide.load();
-        lanes += (int32_t)p.s_int.size();
-        batches += (int32_t)p.plan.size();
+    for (size_t j = 0; j < at.size(); ++j) {
+        if (!over[j]) continue;
+        range_exceeded(gs[at[j]]);
+        alone.push_back(at[j]);
     }
-    int32_t *d_lanes = nullptr;
-    BatchDev *d_devs = nullptr;
-    int2 *d_bt = nullptr;
-    struct Tmp {
-        int32_t *&a;
-        BatchDev *&b;
-        int2 *&c;
-        ~Tmp() {
-            if (a) (void)hipFree(a);
-            if (b) (void)hipFree(b);
-            if (c) (void)hipFree(c);
-        }
-    } tmp_guard{d_lanes, d_devs, d_bt};
-    hipError_t e = hipSuccess;
-    if (batches > 0) {
-        e = hipMalloc(&d_lanes, (size_t)std::max(lanes, 1) * sizeof(int32_t));
-        if (e == hipSuccess) e = hipMalloc(&d_devs, (size_t)batches * sizeof(BatchDev));
-        if (e == hipSuccess) e = hipMalloc(&d_bt, (size_t)batches * sizeof(int2));
-    }
-    // host tables: lanes, batch views and (first lane, lane count) per batch,
-    // the narrow-row graphs' batches first
-    std::vector<int32_t> h_lanes((size_t)std::max(lanes, 1));
-    std::vector<BatchDev> h_devs;
-    std::vector<int2> h_bt;
-    int32_t n_narrow = 0;
-    for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {
-        for (Part &p : parts) {
-            bc_graph_s *g = gs[p.i];
-            const bool narrow = p.narrow;
-            if (narrow != (pass == 0)) continue;
-            auto &f = g->fused;
-            std::copy(p.s_int.begin(), p.s_int.end(), h_lanes.begin() + p.lane0);
-            for (size_t b = 0; b < p.plan.size(); ++b) {
-                BatchDev d = f.h_devs[b];
-                d.narrow = narrow ? 1 : 0;
-                d.stats = nullptr;
-                d.nseg = 0;
-                d.seg_start = nullptr;
-                d.seg_out = nullptr;
-                h_devs.push_back(d);
-                h_bt.push_back(make_int2(p.lane0 + p.plan[b].first, p.plan[b].nlanes));
-            }
-            if (pass == 0) n_narrow += (int32_t)p.plan.size();
-        }
-    }
-    if (h_devs.size() != (size_t)batches || h_bt.size() != (size_t)batches) return BC_ERR_DEVICE;
-    if (e == hipSuccess && batches > 0)
-        e = hipMemcpyAsync(d_lanes, h_lanes.data(), (size_t)lanes * sizeof(int32_t),
-                           hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && batches > 0)
-        e = hipMemcpyAsync(d_devs, h_devs.data(), (size_t)batches * sizeof(BatchDev),
-                           hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && batches > 0)
-        e = hipMemcpyAsync(d_bt, h_bt.data(), (size_t)batches * sizeof(int2),
-                           hipMemcpyHostToDevice, stream);
-    // the launches: narrow rows, then double rows
-    if (e == hipSuccess && n_narrow > 0)
-        e = batch_fused(d_devs, n_narrow, true, d_lanes, d_bt, stream);
-    if (e == hipSuccess && batches > n_narrow)
-        e = batch_fused(d_devs + n_narrow, batches - n_narrow, false, d_lanes, d_bt + n_narrow,
-                        stream);
-    for (Part &p : parts) {
-        if (e != hipSuccess) break;
-        auto &f = gs[p.i]->fused;
-        e = hipMemcpyAsync(f.h_ctrl, f.d_ctrl, p.plan.size() * kCtlInts * sizeof(int32_t),
-                           hipMemcpyDeviceToHost, stream);
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) return from_hip(e);
-    bool range = false;
-    for (Part &p : parts) {
-        bc_graph_s *g = gs[p.i];
-        auto &f = g->fused;
-        const int32_t nb = (int32_t)p.plan.size();
-        bool redo = false, over = false;
-        int32_t depth = 0;
-        for (int32_t b = 0; b < nb; ++b) {
-            const int32_t *c = f.h_ctrl + (size_t)b * kCtlInts;
-            if (c[kCtlNarrow]) {  // a path count needs double rows
-                g->sigma_wide.store(true);
-                redo = true;
-            }
-            if (c[kCtlTrunc]) redo = true;  // a batch ran deeper than the level array
-            over |= c[kCtlRange] != 0;
-            depth = std::max(depth, c[kCtlDeepest]);
-        }
-        if (over) g->sigma_ext.store(true);  // beyond double: level-scaled, host loop
-        if (redo || over) {
-            p.alone = true;
-            continue;
-        }
-        g->batch_depth_hint.store(depth);
-        e = sum_parts(g->n, f.d_bc, nb, f.d_total, stream, false);
-        if (e == hipSuccess) e = gather_f64(g->n, g->d_perm, f.d_total, outs[p.i], stream);
-        if (e != hipSuccess) return from_hip(e);
-    }
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) return from_hip(e);
-    locks.clear();
-    for (const Part &p : parts)
-        if (p.alone) alone.push_back(p.i);
     std::sort(alone.begin(), alone.end());
     for (int32_t i = 0; loops && i < ng; ++i) loops[i] = BC_LOOP_DEVICE;
+    bool range = false;
     for (int32_t i : alone) {
         bc_graph_s *g = gs[i];
-        // as the graph would run alone with the loop it was given (a graph
-        // left out of the launch: the host loop)
-        const int32_t loop = join[(size_t)i] ? BC_LOOP_DEVICE : BC_LOOP_HOST;
-        if (loops) loops[i] = use_fused(g, loop, (ks[i] + kWave - 1) / kWave, kWave)
-                                  ? BC_LOOP_DEVICE : BC_LOOP_HOST;
+        if (loops) loops[i] = BC_LOOP_HOST;
         const bc_status s2 = batched_run(g, sources[i], ks[i], outs[i], kWave,
-                                         g->tuned_sparse_div.load(), 0, loop, stream,
+                                         g->tuned_sparse_div.load(), 0, BC_LOOP_HOST, stream,
                                          nullptr, nullptr);
         if (s2 == BC_ERR_RANGE) range = true;
         else if (s2 != BC_OK) return s2;
     }
     return range ? BC_ERR_RANGE : BC_OK;
-}
-
-// The device-resident loop runs a batch on one compute unit (up to 256
-// batches at once); the host-driven loop runs a batch across the device.
-// Measured on MI355X (R-MAT graphs of 53K to 7.6M arcs): one batch takes about
-// 2 ms + 50 ns per arc on the device loop and, amortised over the host loop's
-// concurrent parts, 0.8 ms + 0.15 ns per arc on the host loop.  AUTO picks
-// the loop with the lower estimate for the call's batch count.
-bool use_fused(const bc_graph_s *g, int32_t level_loop, int32_t nbatches, int32_t width) {
-    if (g->sigma_ext.load()) return false;  // extended range: host loop only
-    if (width > kWave) return false;        // one lane word per vertex only
-    if (level_loop == BC_LOOP_DEVICE) return true;
-    if (level_loop == BC_LOOP_HOST || level_loop == BC_LOOP_GRAPH) return false;
-    const double arcs = (double)g->nnz;
-    const double device = 2e-3 + 50e-9 * arcs;
-    const double host = 0.8e-3 + 0.15e-9 * arcs;
-    const double rounds = std::ceil((double)nbatches / 256.0);
-    return (double)nbatches * host > rounds * device;
 }
 
 // Batches run at once for `concurrency` (0: by workspace size; the choice
@@ -1073,17 +633,36 @@ bc_status make_plan(bc_graph_s *g, const int32_t *sources, int32_t k, int32_t wi
 bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_out,
                       int32_t width, int32_t sparse_div, int32_t concurrency,
                       int32_t level_loop, hipStream_t stream, int32_t *dist, double *sigma) {
+    if (use_source(g, level_loop, k, width)) {
+        std::vector<SourceJob> jobs(1);
+        SourceJob &job = jobs[0];
+        job.g = g;
+        job.s_int.resize((size_t)k);
+        std::vector<int32_t> rows((size_t)k);
+        for (int32_t i = 0; i < k; ++i) {
+            job.s_int[(size_t)i] = g->h_perm[(size_t)sources[i]];
+            rows[(size_t)i] = i;
+        }
+        job.reqs.push_back({0, k, bc_out});
+        if (dist || sigma) {
+            job.export_row = rows.data();
+            job.dist = dist;
+            job.sigma = sigma;
+            const size_t cells = (size_t)k * (size_t)g->n;
+            if (dist) BC_TRY_HIP(hipMemsetAsync(dist, 0xff, cells * sizeof(int32_t), stream));
+            if (sigma) BC_TRY_HIP(hipMemsetAsync(sigma, 0, cells * sizeof(double), stream));
+        }
+        std::vector<char> over;
+        const bc_status st = source_jobs(jobs, stream, over);
+        if (st != BC_OK || !over[0]) return st;
+        // a count beyond double's range sends the call to the host loop
+        range_exceeded(g);
+    }
     std::vector<int32_t> order, s_int;
     std::vector<BatchPlan> plan;
     {
         const bc_status st0 = make_plan(g, sources, k, width, order, s_int, plan);
         if (st0 != BC_OK) return st0;
-    }
-    if (use_fused(g, level_loop, (int32_t)plan.size(), width)) {
-        // a count beyond double's range sends the call to the host loop
-        const bc_status st =
-            fused_run(g, s_int, plan, {}, {}, bc_out, stream, order.data(), dist, sigma);
-        if (st != BC_ERR_RANGE || !g->sigma_ext.load()) return st;
     }
     const int32_t P = parts_of(g, concurrency, (int32_t)plan.size(), width > kWave ? 2 : 1);
     if (P <= 1)
@@ -1158,6 +737,17 @@ bc_status multi_run(bc_graph_s *g, const int32_t *sources, const int32_t *req_st
     const int32_t k = req_start[nreq];
     std::vector<int32_t> s_int((size_t)k);
     for (int32_t i = 0; i < k; ++i) s_int[(size_t)i] = g->h_perm[(size_t)sources[i]];
+    if (multi_source(g)) {
+        std::vector<SourceJob> jobs(1);
+        jobs[0].g = g;
+        jobs[0].s_int = s_int;
+        for (int32_t r = 0; r < nreq; ++r)
+            jobs[0].reqs.push_back({req_start[r], req_start[r + 1] - req_start[r], outs[r]});
+        std::vector<char> over;
+        const bc_status st = source_jobs(jobs, stream, over);
+        if (st != BC_OK || !over[0]) return st;
+        range_exceeded(g);  // the call runs again level-scaled
+    }
     std::vector<BatchPlan> plan;
     std::vector<int32_t> seg_start;
     std::vector<double *> seg_out;
@@ -1198,24 +788,8 @@ bc_status multi_run(bc_graph_s *g, const int32_t *sources, const int32_t *req_st
         hipError_t e = hipMemsetAsync(outs[r], 0, (size_t)g->n * sizeof(double), stream);
         if (e != hipSuccess) return from_hip(e);
     }
-    // the device-resident loop runs a launch's batches at once: only when no
-    // request spans two batches (no two workgroups add to one output)
-    bool spans = false;
-    for (int32_t r = 0; r < nreq; ++r) spans |= req_start[r + 1] - req_start[r] > kWave;
-    if (!spans && use_fused(g, BC_LOOP_AUTO, (int32_t)plan.size(), kWave)) {
-        const bc_status st = fused_run(g, s_int, plan, seg_start, seg_out, nullptr, stream,
-                                       nullptr, nullptr, nullptr);
-        if (st != BC_ERR_RANGE || !g->sigma_ext.load()) return st;
-        // beyond double's range: outputs cleared and the call run again level-scaled
-        for (int32_t r = 0; r < nreq; ++r) {
-            hipError_t e = hipMemsetAsync(outs[r], 0, (size_t)g->n * sizeof(double), stream);
-            if (e != hipSuccess) return from_hip(e);
-        }
-    }
     return run_batch_plan(g, s_int, plan, seg_start, seg_out, nullptr, stream, nullptr, nullptr,
                           nullptr, g->tuned_sparse_div.load(), false);
 }
-
-// Mode selection: BC_MODE_AUTO picks the batched path from the graph's
 
 }  // namespace bcx

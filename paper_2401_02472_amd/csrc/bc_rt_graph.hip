@@ -111,8 +111,7 @@ bc_status set_bc_items(bc_graph_s *g, int32_t cut, int32_t chunk) {
     if (cut < 1 || chunk < kWave || chunk % kWave != 0 || chunk > 4096 || chunk < cut)
         return BC_ERR_INVALID_ARG;
     if (cut == g->bci.cut && chunk == g->bci.chunk) return BC_OK;
-    // idle pooled workspaces go (their partial rows follow the items); the
-    // device-loop pool too
+    // idle pooled workspaces go (their partial rows follow the items)
     (void)bc_trim_workspaces(g);
     if (cut == kB1MaxDeg && chunk == kChunk) {
         reset_bc_items(g);
@@ -279,6 +278,7 @@ bc_status bc_create_graph(int32_t n, const int32_t *row_ptr, const int32_t *col_
         iperm[(size_t)slot] = v;
         g->h_perm[(size_t)v] = slot;
     }
+    while (g->mid_end < n && key_deg(iperm[(size_t)g->mid_end]) > kB0MaxDeg) ++g->mid_end;
     std::vector<int32_t> new_rp((size_t)n + 1, 0), new_rp_in;
     if (directed) new_rp_in.assign((size_t)n + 1, 0);
     for (int32_t u = 0; u < n; ++u) {
@@ -325,17 +325,21 @@ bc_status bc_create_graph(int32_t n, const int32_t *row_ptr, const int32_t *col_
     const size_t pm_bytes = (size_t)std::max(n, 1) * sizeof(int32_t);
     int32_t *t_rp = nullptr, *t_ci = nullptr, *t_rp_in = nullptr, *t_ci_in = nullptr;
     hipError_t e = hipMalloc(&g->d_row_ptr, rp_bytes);
-    if (e == hipSuccess) e = hipMalloc(&g->d_col_idx, ci_bytes);
+    if (e == hipSuccess) e = hipMalloc(&g->d_col_idx, ci_bytes + kArcPad * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc(&g->d_perm, pm_bytes);
     if (e == hipSuccess) e = hipMalloc(&g->d_iperm, pm_bytes);
     if (e == hipSuccess && !on_device) e = hipMalloc(&t_rp, rp_bytes);
     if (e == hipSuccess && !on_device) e = hipMalloc(&t_ci, ci_bytes);
     if (directed) {
         if (e == hipSuccess) e = hipMalloc(&g->d_row_ptr_in, rp_bytes);
-        if (e == hipSuccess) e = hipMalloc(&g->d_col_idx_in, ci_bytes);
+        if (e == hipSuccess)
+            e = hipMalloc(&g->d_col_idx_in, ci_bytes + kArcPad * sizeof(int32_t));
         if (e == hipSuccess) e = hipMalloc(&t_rp_in, rp_bytes);
         if (e == hipSuccess) e = hipMalloc(&t_ci_in, ci_bytes);
     }
+    for (int32_t *col : {g->d_col_idx, g->d_col_idx_in})
+        if (e == hipSuccess && col)
+            e = hipMemsetAsync(col + nnz, 0, kArcPad * sizeof(int32_t), st);
     const int32_t *old_rp = on_device ? row_ptr : t_rp;
     const int32_t *old_ci = on_device ? col_idx : t_ci;
     if (e == hipSuccess && !on_device)
@@ -417,7 +421,8 @@ bc_status bc_destroy_graph(bc_graph_t g) {
     g->plain_pool.clear();
     for (hipStream_t st : g->streams) (void)hipStreamDestroy(st);
     g->streams.clear();
-    fused_release(g);
+    for (SourceWS *ws : g->source_pool) source_ws_destroy(ws);
+    g->source_pool.clear();
     for (BatchWS *ws : g->batch_pool) batch_ws_destroy(ws);
     g->batch_pool.clear();
     free_graph_arrays(g);

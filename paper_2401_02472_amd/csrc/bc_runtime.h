@@ -130,6 +130,18 @@ struct BatchWS {
     ChunkGraphs graphs;        // replayed level chunks (BC_LOOP_GRAPH)
 };
 
+// Workspace of a one-workgroup-per-source launch: scratch of `cap` units
+// (bc_rt_source.hip) and the launch's tables in pinned host memory.
+struct SourceWS {
+    void *block = nullptr;
+    size_t bytes = 0;
+    int32_t cap = 0;
+    char *h_tab = nullptr;
+    size_t tab_cap = 0;
+    unsigned long long *d_stats = nullptr;  // kStatWords counters
+    bool busy = false;
+};
+
 class DeviceGuard {
   public:
     explicit DeviceGuard(int dev) {
@@ -182,7 +194,7 @@ constexpr int kBatchCtrlInts = kCtlInts;
 struct bc_graph_s {
     using PlainWS = bcx::PlainWS;
     using BatchWS = bcx::BatchWS;
-    using BatchDev = bcx::BatchDev;
+    using SourceWS = bcx::SourceWS;
 
     int device = 0;
     int32_t n = 0;
@@ -195,6 +207,7 @@ struct bc_graph_s {
     int32_t b3_end = 0, b2_end = 0, b1_end = 0;  // bucket id ranges
     // batched-path work items (vertices of degree > 64 in kChunk-arc chunks)
     int32_t big_end = 0, multi_end = 0;
+    int32_t mid_end = 0;  // vertices of key degree > 8 (a prefix)
     uint32_t items = 0;
     int2 *d_item_info = nullptr;
     uint32_t *d_item_first = nullptr;
@@ -211,7 +224,7 @@ struct bc_graph_s {
     // The batched BC path's work items: vertices of degree above `cut` (a
     // prefix of the internal order) in chunks of `chunk` arcs, the ones above
     // `chunk` spanning several items.  They start as the tables above (cut 64,
-    // chunk 512), which SSSP, PageRank and the device-resident loop keep; a
+    // chunk 512), which SSSP and PageRank keep; a
     // small graph then takes finer ones (kFineCut, kFineChunk), and
     // bc_autotune or bc_set_work_items may rebuild them with other thresholds
     // (owned: separate device arrays).
@@ -266,23 +279,8 @@ struct bc_graph_s {
     // internal streams for batches run at once (created on first use)
     std::mutex stream_mu;
     std::vector<hipStream_t> streams;
-    // workspaces of the device-resident level loop (one per batch of a launch)
-    std::mutex fused_mu;
-    struct Fused {
-        void *block = nullptr;
-        size_t bytes = 0;
-        int32_t cap = 0, lcap = 0;
-        BatchDev *d_devs = nullptr;
-        int32_t *h_ctrl = nullptr;  // pinned [cap][kCtlInts]
-        int32_t *d_ctrl = nullptr;  // [cap][kCtlInts]
-        double *d_bc = nullptr;     // [cap][n] per-batch BC (internal order)
-        double *d_total = nullptr;  // [n] running BC total of a run (not in the pool)
-        int32_t *d_lanes = nullptr;
-        size_t lanes_cap = 0;
-        int2 *d_batches = nullptr;
-        unsigned long long *d_stats = nullptr;  // kStatWords work counters
-        std::vector<BatchDev> h_devs;
-    } fused;
+    // workspaces of the one-workgroup-per-source path
+    std::vector<SourceWS *> source_pool;
     // hop distances (internal order, -1 unreached) from two landmarks: the
     // highest-degree vertex and the vertex farthest from it; batches are formed
     // from sources sorted by them
@@ -318,10 +316,6 @@ void set_items(const bc_graph_s *g, BatchDev &d);
 size_t batch_ws_bytes(const bc_graph_s *g, int32_t H);
 size_t batch_level_bytes(const bc_graph_s *g, int32_t lcap, int32_t H);
 void batch_ws_destroy(BatchWS *ws);
-size_t fused_batch_bytes(const bc_graph_s *g, int32_t lcap);
-int32_t fused_cap(const bc_graph_s *g, int32_t nbatches, int32_t lcap);
-void fused_release(bc_graph_s *g);
-bool use_fused(const bc_graph_s *g, int32_t level_loop, int32_t nbatches, int32_t width);
 int32_t parts_of(const bc_graph_s *g, int32_t concurrency, int32_t nbatches, int32_t H);
 bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_out,
                       int32_t width, int32_t sparse_div, int32_t concurrency,
@@ -349,6 +343,33 @@ hipError_t drive_batch(bc_graph_s *g, BatchDev &d, const ExtTables &ext, const i
                        unsigned long long *d_stats, int32_t stride, BatchOutcome &how,
                        int32_t &deepest, ChunkGraphs *cg, bool wide_ok);
 
+// ---- one workgroup per source (bc_rt_source.hip) ----
+// One request of a job: sources [first, first + k) of its s_int, into out
+// (device, caller order).
+struct SourceReq {
+    int32_t first, k;
+    double *out;
+};
+// A graph's requests; dist / sigma: exports (device, caller order), source i
+// in row export_row[i].
+struct SourceJob {
+    bc_graph_s *g = nullptr;
+    std::vector<int32_t> s_int;
+    std::vector<SourceReq> reqs;
+    const int32_t *export_row = nullptr;
+    int32_t *dist = nullptr;
+    double *sigma = nullptr;
+};
+bool use_source(const bc_graph_s *g, int32_t level_loop, int32_t k, int32_t width);
+bool source_beats_plain(const bc_graph_s *g, int32_t k);
+// Whether bc_run_multi's calls take it: by the graph alone, so that a
+// request's result does not depend on the requests it shares a call with.
+bool multi_source(const bc_graph_s *g);
+size_t source_bytes(const bc_graph_s *g, int32_t k);
+void source_ws_destroy(SourceWS *ws);
+bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
+                      std::vector<char> &over);
+
 // ---- graph residency (bc_rt_graph.hip) ----
 void free_graph_arrays(bc_graph_s *g);
 // Rebuild the batched BC path's work items with degree cut `cut` (vertices of
@@ -356,12 +377,8 @@ void free_graph_arrays(bc_graph_s *g);
 // pooled batched workspace (their partial rows follow the item count).  No run
 // on g may be in flight.
 bc_status set_bc_items(bc_graph_s *g, int32_t cut, int32_t chunk);
-// The tables built at creation (cut 64, chunk 512): the device-resident loop
-// always runs on them (its 16 waves per batch gain nothing from finer items).
-bc_graph_s::BcItems base_items(const bc_graph_s *g);
-
 // ---- policy and argument checks (bc_capi.hip) ----
-void plain_overflowed(bc_graph_s *g);
+void range_exceeded(bc_graph_s *g);
 bool use_batched(const bc_graph_s *g, const bc_options *opt, int32_t k);
 int32_t batch_width_of(const bc_graph_s *g, const bc_options *opt, int32_t k);
 int32_t sparse_div_of(const bc_graph_s *g, const bc_options *opt);

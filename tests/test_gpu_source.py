@@ -1,0 +1,123 @@
+"""GPU parity of the device-resident level loop (one workgroup per source)
+where its kernel can go wrong: the largest graph whose values fit LDS and the
+first that does not, the degree classes' edges (8 / 9, 64 / 65, 512 / 513
+arcs), arcs that lead back many levels in directed graphs, several sources per
+workgroup, several launches per call, and requests that share a call."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle
+import paper_2401_02472_amd as bcm
+from tests.gpu_checks import batched, check_bc, check_sigma, oracle_bc
+
+pytestmark = pytest.mark.gpu
+
+MAX_N = 20415  # (160 KB - 512) / 8 - 1 values
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    bcm.load_library()
+
+
+def _hubs(degrees, leaves):
+    """A cycle of hubs, hub i with degrees[i] arcs (2 of them along the cycle),
+    the rest to shared leaves chosen in turn."""
+    h = len(degrees)
+    pairs, at = [(i, (i + 1) % h) for i in range(h)], 0
+    for i, d in enumerate(degrees):
+        for _ in range(d - 2):
+            pairs.append((i, h + at % leaves))
+            at += 1
+    p = np.array(pairs)
+    return gg.csr_from_edges(h + leaves, p[:, 0], p[:, 1])
+
+
+def _device(G, src):
+    return batched(G, src, level_loop=bcm.BC_LOOP_DEVICE)
+
+
+@pytest.mark.parametrize("g", [
+    _hubs([7, 8, 9, 10, 63, 64, 65, 66, 511, 512, 513, 514, 1025, 3, 4, 5], 1500),
+    _hubs([64, 65, 66, 67, 68, 127, 128, 129, 255, 256, 257], 300),
+    gg.path(3), gg.star(2), gg.complete(70), gg.cycle(700),
+    gg.erdos_renyi(MAX_N, 6, seed=1), gg.erdos_renyi(MAX_N + 1, 6, seed=1),
+], ids=["hubs", "hubs16", "path3", "edge", "K70", "cycle", "largest", "too-large"])
+def test_classes_and_size_limit(g):
+    src = gg.sample_sources(g, min(g.n, 40), seed=2)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        got = _device(G, src)
+        check_bc(got, oracle_bc(g, src))
+        assert np.array_equal(got, _device(G, src))
+        opt = bcm.make_options(bcm.BC_MODE_BATCHED, level_loop=bcm.BC_LOOP_DEVICE)
+        _, dist, sigma = G.run_detail(src[:3], opt)
+        for i in range(min(3, src.size)):
+            od, osg, _, _ = oracle.single_source(g.row_ptr, g.col_idx, int(src[i]), with_delta=False)
+            assert np.array_equal(dist[i], od)
+            check_sigma(sigma[i], osg)
+        # the measured run is another instance of the kernel
+        G.profile_enable(True)
+        assert np.array_equal(got, _device(G, src))
+        G.profile_enable(False)
+
+
+def test_directed_arcs_back_to_early_levels():
+    """A long directed path whose vertices also point back to vertices of every
+    earlier level (and of every residue of the level), joined to a dense part."""
+    n = 60
+    pairs = [(i, i + 1) for i in range(n - 1)]
+    pairs += [(i, j) for i in range(n) for j in range(i) if (i * 7 + j) % 3 == 0]
+    rng = np.random.default_rng(4)
+    pairs += [(int(a), int(b)) for a, b in rng.integers(0, 400, (3000, 2)) if a != b]
+    g = gg.directed(400, pairs, "back-arcs")
+    src = np.arange(0, 400, 3, dtype=np.int32)
+    want, st = oracle.bc(g.row_ptr, g.col_idx, src, directed=True)
+    assert st == oracle.OK
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx, flags=bcm.BC_GRAPH_DIRECTED) as G:
+        check_bc(_device(G, src), want)
+        check_bc(_device(G, src[:1]), oracle.bc(g.row_ptr, g.col_idx, src[:1], directed=True)[0])
+
+
+@pytest.mark.parametrize("k", [1, 512, 513, 1300])
+def test_several_sources_per_workgroup(k):
+    g = gg.rmat(11, 8, seed=5)
+    src = gg.sample_sources(g, k, seed=6)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        got = _device(G, src)
+        check_bc(got, oracle_bc(g, src))
+        assert np.array_equal(got, _device(G, src))
+
+
+def test_requests_over_several_launches_equal_alone():
+    """More units than a launch's scratch holds (512 MB at 0.7 MB each): small
+    requests before and after a large one whose units two launches share."""
+    import torch
+    g = gg.erdos_renyi(20000, 5, seed=7)
+    sizes = [1] * 380 + [700] + [0] + [2] * 120
+    reqs = [gg.sample_sources(g, k, seed=100 + i) if k else np.zeros(0, np.int32)
+            for i, k in enumerate(sizes)]
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        outs = [torch.full((g.n,), -1.0, dtype=torch.float64, device="cuda") for _ in reqs]
+        G.run_multi(reqs, outs)
+        torch.cuda.synchronize()
+        for i in (0, 200, 379, 380, 381, 382, len(reqs) - 1):
+            alone = torch.full((g.n,), -1.0, dtype=torch.float64, device="cuda")
+            G.run_multi([reqs[i]], [alone])
+            got = outs[i].cpu().numpy()
+            assert np.array_equal(got, alone.cpu().numpy()), f"request {i}"
+            check_bc(got, oracle_bc(g, reqs[i]) if sizes[i] else np.zeros(g.n))
+
+
+def test_workspaces_are_reported_and_trimmed():
+    g = gg.rmat(12, 8, seed=8)
+    src = gg.sample_sources(g, 100, seed=9)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        opt = bcm.make_options(bcm.BC_MODE_BATCHED, level_loop=bcm.BC_LOOP_DEVICE)
+        want = _device(G, src)
+        assert 0 < G.workspace_held() <= G.workspace_bytes(100, opt)
+        G.trim_workspaces()
+        assert G.workspace_held() == 0
+        assert np.array_equal(want, _device(G, src))
