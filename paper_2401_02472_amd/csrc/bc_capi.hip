@@ -22,10 +22,13 @@ bool use_batched(const bc_graph_s *g, const bc_options *opt, int32_t k) {
     if (mode == BC_MODE_BATCHED) return true;
     if (mode == BC_MODE_PLAIN) return false;
     if (k >= g->tuned_min_batched.load()) return true;
+    const int32_t loop = opt ? opt->level_loop : BC_LOOP_AUTO;
+    const int32_t width = batch_width_of(g, opt, k);
+    // a graph found deep: every source's level steps together
+    if (use_pair(g, loop, width)) return true;
     // few sources: a workgroup per source (a batched loop) against the
     // one-source path, which spreads each source over the device
-    return use_source(g, opt ? opt->level_loop : BC_LOOP_AUTO, k, batch_width_of(g, opt, k)) &&
-           source_beats_plain(g, k);
+    return use_source(g, loop, k, width) && source_beats_plain(g, k);
 }
 
 int32_t batch_width_of(const bc_graph_s *g, const bc_options *opt, int32_t k) {
@@ -276,6 +279,8 @@ bc_status bc_workspace_bytes(bc_graph_t g, int32_t k, const bc_options *opt, siz
     const int32_t lcap = std::max(16, g->batch_depth_hint.load() + 8);
     if (use_source(g, opt ? opt->level_loop : 0, k, width)) {
         *bytes = source_bytes(g, k);
+    } else if (use_pair(g, opt ? opt->level_loop : 0, width)) {
+        *bytes = pair_bytes(g, k);
     } else {
         // one workspace per concurrent part
         const int32_t parts = parts_of(g, opt ? opt->concurrency : 0, nb, H);
@@ -307,6 +312,7 @@ bc_status bc_workspace_held(bc_graph_t g, size_t *bytes) {
         for (const BatchWS *ws : g->batch_pool)
             b += ws->bytes + (ws->lcap ? batch_level_bytes(g, ws->lcap, ws->H) : 0) + ws->src_cap;
         for (const SourceWS *ws : g->source_pool) b += ws->bytes;
+        for (const PairWS *ws : g->pair_pool) b += ws->bytes;
     }
     *bytes = b;
     return BC_OK;
@@ -318,6 +324,7 @@ bc_status bc_trim_workspaces(bc_graph_t g) {
     std::vector<PlainWS *> idle;
     std::vector<BatchWS *> idle_b;
     std::vector<SourceWS *> idle_s;
+    std::vector<PairWS *> idle_p;
     {
         std::lock_guard<std::mutex> lk(g->mu);
         std::vector<PlainWS *> keep;
@@ -329,10 +336,14 @@ bc_status bc_trim_workspaces(bc_graph_t g) {
         std::vector<SourceWS *> keep_s;
         for (SourceWS *ws : g->source_pool) (ws->busy ? keep_s : idle_s).push_back(ws);
         g->source_pool.swap(keep_s);
+        std::vector<PairWS *> keep_p;
+        for (PairWS *ws : g->pair_pool) (ws->busy ? keep_p : idle_p).push_back(ws);
+        g->pair_pool.swap(keep_p);
     }
     for (PlainWS *ws : idle) plain_ws_destroy(ws);
     for (BatchWS *ws : idle_b) batch_ws_destroy(ws);
     for (SourceWS *ws : idle_s) source_ws_destroy(ws);
+    for (PairWS *ws : idle_p) pair_ws_destroy(ws);
     return BC_OK;
 }
 
@@ -341,7 +352,7 @@ bc_status bc_trim_workspaces(bc_graph_t g) {
 // with part of a wave inactive, over every kernel file, since the last call.
 unsigned int bc_debug_exec_partial(void) {
     return exec_partial_batched() + exec_partial_plain() + exec_partial_sssp() +
-           exec_partial_pagerank() + exec_partial_source();
+           exec_partial_pagerank() + exec_partial_source() + exec_partial_pair();
 }
 #endif
 

@@ -4,8 +4,10 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
+#include <utility>
 
 namespace bcx {
 
@@ -211,6 +213,7 @@ unsigned int exec_partial_plain();
 unsigned int exec_partial_sssp();
 unsigned int exec_partial_pagerank();
 unsigned int exec_partial_source();
+unsigned int exec_partial_pair();
 #endif
 
 // Launchers (bc_batched.hip).  All are asynchronous on `stream`.
@@ -285,6 +288,63 @@ hipError_t source_run(const SourceUnit *units, int32_t nunits, const SourceGraph
                       const int32_t *sources, bool directed, size_t lds, int32_t *range,
                       unsigned long long *stats, hipStream_t stream);
 hipError_t source_sum(const SourceSum *sums, int32_t nsums, int32_t max_n, hipStream_t stream);
+
+// Brandes over (vertex, source) pairs (bc_pair.hip): one part's arrays, each
+// [k][stride] (stride: n rounded up to 16) unless noted.
+constexpr int kPairMaxDeg = 16;  // most arcs of a vertex on this path
+
+struct PairGraph {
+    const int32_t *row_ptr, *col_idx;  // in the pair path's vertex order
+    const int4 *four;                  // see LayoutDev
+};
+
+struct PairDev {
+    int32_t n, k;             // sources 0 .. k-1
+    int32_t lcap;             // levels cnt and lvl hold
+    size_t stride;
+    PairGraph g;
+    const int32_t *src;       // [k] internal ids
+    const int32_t *pos;       // [n] internal id -> vertex of these arrays
+    int32_t *at;              // [k] the sources there
+    int32_t *q;               // vertices in level order
+    uint8_t *code;            // level mod 3, 3 = not reached (NULL: one workgroup per source)
+    double *val;              // sigma, then (1 + delta) / sigma
+    double *delta;
+    double *sig;              // one workgroup per source: sigma in queue order
+    int32_t *ex;              // extended range (else NULL): val = stored 2^ex
+    int32_t *cnt, *lvl;       // [lcap][k] vertices and first queue position of a level
+                              // (one workgroup per source: lvl [k][lcap] alone)
+    int32_t *depth;           // [k] deepest level so far
+    int32_t *range;           // set where a count passes double's range
+    unsigned long long *stats;  // NULL, or work counters
+};
+
+// The pair path's vertex order (bc_layout.hip): inputs, scratch and results.
+struct LayoutDev {
+    int32_t n;
+    const int32_t *row_ptr, *col_idx, *iperm;
+    int32_t *tmp[6];       // [n + 1] each
+    int32_t *pos;          // [n] internal id -> place
+    int32_t *new_rp;       // [n + 1] the CSR in that order
+    int32_t *new_col;      // [nnz]
+    int4 *four;            // [n] the first four arcs of a vertex, -1 past its last
+    int32_t *caller;       // [n] place -> caller id
+};
+// first entry of `four` for a vertex of more than four arcs
+constexpr int32_t kMoreArcs = -2;
+hipError_t layout_build(const LayoutDev &d, hipStream_t stream);
+
+hipError_t pair_start(const PairDev &d, hipStream_t stream);
+// One level step; `per` workgroups per source.
+hipError_t pair_forward(const PairDev &d, int32_t level, int32_t per, hipStream_t stream);
+hipError_t pair_reverse(const PairDev &d, int32_t level, int32_t per, hipStream_t stream);
+// One workgroup per source: the arrays cleared (pass 0), the forward pass (1;
+// depth -1 where the levels did not fit), the reverse pass (2).
+hipError_t deep_source(const PairDev &d, int pass, hipStream_t stream);
+size_t deep_lds_bytes(int32_t n);
+// out (caller order) = the sources' dependencies, added to it with `carry`.
+hipError_t pair_sum(const PairDev &d, const int32_t *caller, double *out, bool carry,
+                    hipStream_t stream);
 
 // Device view of a single-source shortest-path run (bc_sssp.hip): the graph's
 // out-arcs with their weights (NULL: every arc weighs 1), the same chunk items

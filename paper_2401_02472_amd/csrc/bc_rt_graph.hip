@@ -268,6 +268,7 @@ bc_status bc_create_graph(int32_t n, const int32_t *row_ptr, const int32_t *col_
         while (c < 32 && ((int64_t)1 << c) <= kd) ++c;
         g->deg_class[c]++;
     }
+    g->max_deg = maxdeg;
     std::vector<int64_t> start((size_t)maxdeg + 2, 0);
     for (int32_t v = 0; v < n; ++v) start[(size_t)(maxdeg - key_deg(v)) + 1]++;
     for (size_t i = 1; i < start.size(); ++i) start[i] += start[i - 1];
@@ -423,6 +424,9 @@ bc_status bc_destroy_graph(bc_graph_t g) {
     g->streams.clear();
     for (SourceWS *ws : g->source_pool) source_ws_destroy(ws);
     g->source_pool.clear();
+    for (PairWS *ws : g->pair_pool) pair_ws_destroy(ws);
+    g->pair_pool.clear();
+    if (g->layout.block) (void)hipFree(g->layout.block);
     for (BatchWS *ws : g->batch_pool) batch_ws_destroy(ws);
     g->batch_pool.clear();
     free_graph_arrays(g);

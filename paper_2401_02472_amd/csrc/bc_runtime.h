@@ -142,6 +142,18 @@ struct SourceWS {
     bool busy = false;
 };
 
+// Workspace of a pair-path call (bc_rt_pair.hip).
+struct PairWS {
+    LaunchTimer timer;
+    unsigned long long *d_stats = nullptr;  // kStatWords counters
+    void *block = nullptr;
+    size_t bytes = 0;
+    int32_t *h_depth = nullptr;  // pinned [depth_cap] depths and range flag, then the sources
+    int32_t depth_cap = 0;
+    PairDev dev{};
+    bool busy = false;
+};
+
 class DeviceGuard {
   public:
     explicit DeviceGuard(int dev) {
@@ -195,6 +207,7 @@ struct bc_graph_s {
     using PlainWS = bcx::PlainWS;
     using BatchWS = bcx::BatchWS;
     using SourceWS = bcx::SourceWS;
+    using PairWS = bcx::PairWS;
 
     int device = 0;
     int32_t n = 0;
@@ -208,6 +221,7 @@ struct bc_graph_s {
     // batched-path work items (vertices of degree > 64 in kChunk-arc chunks)
     int32_t big_end = 0, multi_end = 0;
     int32_t mid_end = 0;  // vertices of key degree > 8 (a prefix)
+    int32_t max_deg = 0;  // largest key degree
     uint32_t items = 0;
     int2 *d_item_info = nullptr;
     uint32_t *d_item_first = nullptr;
@@ -276,11 +290,26 @@ struct bc_graph_s {
     // set once a path count overflowed double: later batches keep level-scaled
     // counts (extended range, host-driven loop only)
     std::atomic<bool> sigma_ext{false};
+    // set once a batch ran deeper than kPairDepth levels: later calls take the
+    // pair path where the graph's degrees allow it, with exponents once a
+    // count passed double's range
+    std::atomic<bool> deep{false};
+    std::atomic<bool> pair_ext{false};
+    // the pair path's vertex order and the CSR in it (built on first use)
+    std::mutex layout_mu;
+    struct Layout {
+        void *block = nullptr;
+        int32_t *pos = nullptr, *row_ptr = nullptr, *col_idx = nullptr, *caller = nullptr;
+        int4 *four = nullptr;
+    } layout;
+    std::atomic<int32_t> pair_depth_hint{0};  // levels of the last pair-path run
     // internal streams for batches run at once (created on first use)
     std::mutex stream_mu;
     std::vector<hipStream_t> streams;
     // workspaces of the one-workgroup-per-source path
     std::vector<SourceWS *> source_pool;
+    // ... and of the pair path
+    std::vector<PairWS *> pair_pool;
     // hop distances (internal order, -1 unreached) from two landmarks: the
     // highest-degree vertex and the vertex farthest from it; batches are formed
     // from sources sorted by them
@@ -333,15 +362,16 @@ struct ExtTables {
 };
 // Rerun: run the batch again (the graph's rows became wider); Grow: with a
 // longer level array; NeedWide: the graph takes double rows and the
-// workspace's sigma rows are uint32-sized: widen them, then run the batch.
-enum class BatchOutcome { Done, Rerun, Grow, NeedWide };
+// workspace's sigma rows are uint32-sized: widen them, then run the batch;
+// Deep: the graph is one for the pair path (only with `deep_ok`).
+enum class BatchOutcome { Done, Rerun, Grow, NeedWide, Deep };
 // cg: replay the level chunks as captured graphs (NULL: launch every step).
 // wide_ok: d's sigma rows hold doubles (else uint32 only: a graph that takes
 // double rows gets NeedWide before anything is launched).
 hipError_t drive_batch(bc_graph_s *g, BatchDev &d, const ExtTables &ext, const int32_t *lanes_dev,
                        int32_t nl, int32_t *h_ctrl, hipStream_t stream, LaunchTimer &timer,
                        unsigned long long *d_stats, int32_t stride, BatchOutcome &how,
-                       int32_t &deepest, ChunkGraphs *cg, bool wide_ok);
+                       int32_t &deepest, ChunkGraphs *cg, bool wide_ok, bool deep_ok = false);
 
 // ---- one workgroup per source (bc_rt_source.hip) ----
 // One request of a job: sources [first, first + k) of its s_int, into out
@@ -369,6 +399,17 @@ size_t source_bytes(const bc_graph_s *g, int32_t k);
 void source_ws_destroy(SourceWS *ws);
 bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
                       std::vector<char> &over);
+
+// ---- pairs (bc_rt_pair.hip) ----
+// A batch that is not finished after this many levels makes its graph a deep
+// one.
+constexpr int32_t kPairDepth = 48;
+bool pair_fits(const bc_graph_s *g);
+bool use_pair(const bc_graph_s *g, int32_t level_loop, int32_t width);
+size_t pair_bytes(const bc_graph_s *g, int32_t k);
+void pair_ws_destroy(PairWS *ws);
+bc_status pair_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_out,
+                   hipStream_t stream);
 
 // ---- graph residency (bc_rt_graph.hip) ----
 void free_graph_arrays(bc_graph_s *g);

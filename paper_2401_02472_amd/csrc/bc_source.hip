@@ -176,6 +176,7 @@ __device__ __forceinline__ void over_row(const SrcView &s, const int32_t *col, R
                                          Body &&body) {
     Ids nx = ids_at(col, r);
     while (__ballot(r.e < r.re)) {
+        BC_FULL_EXEC();
         Ids x = nx;
         const int left = r.re - r.e;
         r.e += 4 * W;

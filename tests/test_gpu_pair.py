@@ -1,0 +1,151 @@
+"""GPU parity of the pair path (deep graphs of low degree: per-source queues of
+a level's vertices) against the oracle, and where a graph is found deep."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+import paper_2401_02472_amd as bcm
+from tests.gpu_checks import batched, check_bc, oracle_bc, oracle_bc_ext, plain, run_mode
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    bcm.load_library()
+
+
+def _auto(G, src):
+    return run_mode(G, src, bcm.BC_MODE_AUTO)
+
+
+def _deg16():
+    """A long chain of vertices of exactly 16 arcs (8 parallel arcs to each
+    neighbour) with self-loops' worth of room left, and pendant paths."""
+    n, h = 21000, 60
+    a = [(i, i + 1) for i in range(h) for _ in range(8)]
+    b = [(h + 1 + i, h + 2 + i) for i in range(n - h - 2)]
+    b += [(0, n - 1), (h, h + 1)]
+    p = np.array(a + b)
+    return gg.csr_from_edges(n, p[:, 0], p[:, 1], dedup=False)
+
+
+def _island_grid():
+    """A road-like grid beside isolated vertices and a short second component."""
+    g = gg.grid_road(150, 150, seed=3)
+    src = np.repeat(np.arange(g.n), np.diff(g.row_ptr))
+    keep = src < g.col_idx
+    u = np.concatenate([src[keep], [g.n + 10, g.n + 11, g.n + 11]])
+    v = np.concatenate([g.col_idx[keep], [g.n + 11, g.n + 12, g.n + 13]])
+    return gg.csr_from_edges(g.n + 20, u, v)
+
+
+@pytest.mark.parametrize("g,k", [
+    (gg.grid_road(150, 150, seed=1), 1), (gg.grid_road(150, 150, seed=1), 2),
+    (gg.grid_road(300, 211, 0.05, 0.0, seed=2), 16), (gg.grid_road(160, 131, seed=5), 64),
+    (gg.grid_road(160, 131, seed=5), 65), (gg.grid_road(160, 131, seed=5), 200),
+    (_island_grid(), 70), (_deg16(), 40),
+], ids=["k1", "k2", "deep16", "k64", "k65", "k200", "islands", "deg16"])
+def test_parity(g, k):
+    src = gg.sample_sources(g, k, seed=7)
+    if g.n == 150 * 150 + 20:  # duplicates, an isolated source, the second component
+        src[:6] = [5, 5, g.n - 20, g.n - 9, g.n - 8, g.n - 1]
+    want = oracle_bc(g, src)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        first = batched(G, src)           # found deep on the way (or by what follows)
+        check_bc(first, want)
+        check_bc(plain(G, src[:2]), oracle_bc(g, src[:2]))
+        got = batched(G, src)             # pairs from the first level on
+        check_bc(got, want)
+        assert np.array_equal(got, batched(G, src))
+        check_bc(_auto(G, src[:1]), oracle_bc(g, src[:1]))
+        check_bc(_auto(G, src[:3]), oracle_bc(g, src[:3]))
+        # the loops that a caller names stay themselves
+        host = batched(G, src, level_loop=bcm.BC_LOOP_HOST)
+        assert np.array_equal(host, batched(G, src, level_loop=bcm.BC_LOOP_GRAPH))
+        check_bc(host, want)
+
+
+def test_profiled_run_counts_the_pairs():
+    """Work counters of a profiled run: every reached (vertex, source) pair once
+    per pass (the sources themselves in the forward pass only)."""
+    g = gg.grid_road(160, 140, seed=8)
+    src = gg.sample_sources(g, 20, seed=9)
+    want = oracle_bc(g, src)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        batched(G, src)
+        _, dist, _ = G.run_detail(src, bcm.make_options(bcm.BC_MODE_BATCHED))
+        reached = int((dist >= 0).sum())
+        G.profile_enable(True)
+        G.profile_read(reset=True)
+        check_bc(batched(G, src), want)
+        p = G.profile_read(reset=True)
+        assert p["forward"]["owners"] == reached
+        assert p["reverse"]["owners"] == reached - src.size
+        # each DAG arc once per pass, but for the arcs out of the sources
+        first = sum(int((dist[i][g.col_idx[g.row_ptr[s]:g.row_ptr[s + 1]]] == 1).sum())
+                    for i, s in enumerate(src))
+        assert p["reverse"]["hits"] == p["forward"]["hits"] - first
+
+
+def test_counts_beyond_double_range():
+    """A lattice whose counts pass double's range: found on the way, run again
+    with exponents, and with them from the start in later calls."""
+    g = gg.grid_full(600, 600)
+    src = np.array([0, 599, 180300, 359999] + list(range(7, 340000, 28000)), np.int32)
+    want = oracle_bc_ext(g, src)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        check_bc(batched(G, src), want)
+        check_bc(batched(G, src), want)
+        check_bc(_auto(G, src), want)
+        # sources whose counts fit give the same with exponents as without
+    small = np.array([180300, 180301], np.int32)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        plain(G, small[:1])
+        a = _auto(G, small)
+        check_bc(a, oracle_bc(g, small))
+        _auto(G, src)
+        assert np.array_equal(a, _auto(G, small))
+
+
+@pytest.mark.parametrize("rows,cols,short,k,ext", [
+    (700, 701, 0.001, 2, False),    # wide levels, few sources: a launch per level
+    (1150, 1147, 0.001, 3, False),  # past the vertices whose visited bits fit LDS
+    (1150, 1147, 0.0, 2, True),     # ... and counts past double's range
+], ids=["wide", "large", "large-ext"])
+def test_launch_per_level(rows, cols, short, k, ext):
+    g = gg.grid_road(rows, cols, 0.0 if ext else 0.05, short, seed=12)
+    src = gg.sample_sources(g, k, seed=13)
+    if ext:
+        src[0] = 0
+    want = oracle_bc_ext(g, src) if ext else oracle_bc(g, src)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        for _ in range(3):
+            got = batched(G, src)
+            check_bc(got, want)
+        assert np.array_equal(got, batched(G, src))
+
+
+def test_more_levels_than_the_first_estimate_and_trim():
+    g = gg.path(21000)
+    src = np.array([0, 20999, 10000, 3], np.int32)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        for _ in range(2):
+            check_bc(batched(G, src), oracle_bc(g, src))
+        assert 0 < G.workspace_held()
+        G.trim_workspaces()
+        assert G.workspace_held() == 0
+        check_bc(_auto(G, src), oracle_bc(g, src))
+
+
+def test_rounds_of_sources():
+    """More sources than a round's scratch holds (3.4 MB each of 4 GB)."""
+    g = gg.grid_road(400, 400, seed=10)
+    ten = gg.sample_sources(g, 13, seed=11)
+    src = np.tile(ten, 100)
+    want = 100.0 * oracle_bc(g, ten)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        check_bc(batched(G, ten), oracle_bc(g, ten))
+        check_bc(batched(G, src), want)
