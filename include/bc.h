@@ -106,7 +106,8 @@ typedef struct bc_options {
                             nnz / sparse_div arcs expands from the frontier (visits only
                             the frontier's neighbours) instead of scanning every
                             unvisited vertex; 1..2^20, -1 = never, 0 = the graph's
-                            setting (bc_autotune's choice, else 64)                      */
+                            setting (bc_autotune's choice, else 64, or never for up to
+                            131,072 vertices)                                           */
     int32_t concurrency; /* batched mode: batches run at once, each with its own
                             workspace and stream, 1..8 (0 = by workspace size: 4 up to
                             1 GB, 2 up to 16 GB, else 1); BC is the sum of the parts in
@@ -225,10 +226,10 @@ bc_status bc_run_async_noalloc(bc_graph_t g, const int32_t *sources, int32_t k,
  *   bc_outs    [nreq] host array of device pointers, each to n doubles, overwritten
  *              with that request's BC (caller vertex order) by the end of the
  *              call's work on `stream`
- * Sources of different requests share the 64-source batches.  A request of at
- * most 64 sources never straddles two batches, and a larger one always splits
- * at the same positions, so each request's result is bit-identical to the one
- * it gets alone.  Waits on `stream` like bc_run_async.  Errors: as
+ * Sources of different requests share the 64-source batches (on small graphs,
+ * a launch of one workgroup per source).  A request of at most 64 sources never
+ * straddles two batches, and a larger one always splits at the same positions,
+ * so each request's result is bit-identical to the one it gets alone.  Waits on `stream` like bc_run_async.  Errors: as
  * bc_run_async; BC_ERR_INVALID_ARG also for a decreasing req_start or a NULL
  * output.
  */

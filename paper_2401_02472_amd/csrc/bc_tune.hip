@@ -227,14 +227,15 @@ bc_status bc_autotune(bc_graph_t g, const int32_t *sources, int32_t k, void *str
     // replaces the current choice only when it is more than 2 % faster (on
     // one sample batch, near-equal settings swap places from run to run).
     constexpr double kTuneMargin = 0.98;
-    const int32_t divs[] = {kDefaultSparseDiv, -1, 16, 256};
+    const int32_t untuned = g->n <= kNoSparseN ? -1 : kDefaultSparseDiv;
+    const int32_t divs[] = {untuned, untuned == -1 ? kDefaultSparseDiv : -1, 16, 256};
     double div_ms = 1e30;
-    int32_t best_div = kDefaultSparseDiv;
+    int32_t best_div = untuned;
     for (int32_t div : divs) {
         double ms = 0;
         st = batched(m64, kWave, div, ms);
         if (st != BC_OK) break;
-        if (div == kDefaultSparseDiv || ms < div_ms * kTuneMargin) {
+        if (div == untuned || ms < div_ms * kTuneMargin) {
             div_ms = ms;
             best_div = div;
         }
