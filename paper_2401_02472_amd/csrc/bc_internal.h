@@ -372,8 +372,11 @@ struct SsspDev {
 // two share buffers (iteration i reads [i & 1], writes [(i + 1) & 1]), chunk
 // partials of the split vertices, per-wave change slots (2 sets) and the
 // change of every iteration (-1 = not run).
+// Vertices whose shares a PageRank workgroup can hold in LDS (159 of 160 KB).
+constexpr int32_t kPrHubs = 20352;
 struct PrDev {
     int32_t n;
+    int64_t nnz, hub_arcs;  // arcs; those out of the first kPrHubs vertices
     int32_t big_end, multi_end;
     uint32_t items_in;
     const int32_t *row_ptr;

@@ -157,6 +157,8 @@ bc_status bc_pagerank(bc_graph_t g, double damping, double tol, int32_t max_iter
     }
     PrDev d{};
     d.n = g->n;
+    d.nnz = g->nnz;
+    d.hub_arcs = g->hub_arcs;
     d.big_end = g->big_end;
     d.multi_end = g->multi_end;
     d.items_in = g->items_in;

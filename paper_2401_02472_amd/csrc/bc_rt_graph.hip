@@ -294,6 +294,7 @@ bc_status bc_create_graph(int32_t n, const int32_t *row_ptr, const int32_t *col_
         if (b >= 2) g->b2_end = u + 1;
         if (b >= 1) g->b1_end = u + 1;
     }
+    g->hub_arcs = new_rp[(size_t)std::min(n, kPrHubs)];
     uint64_t chunks = 0;
     for (int32_t u = 0; u < g->b3_end; ++u) chunks += chunks_of(out_deg(iperm[(size_t)u]));
     g->total_chunks3 = chunks;

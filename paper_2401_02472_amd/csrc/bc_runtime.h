@@ -222,6 +222,7 @@ struct bc_graph_s {
     int32_t big_end = 0, multi_end = 0;
     int32_t mid_end = 0;  // vertices of key degree > 8 (a prefix)
     int32_t max_deg = 0;  // largest key degree
+    int64_t hub_arcs = 0;  // arcs out of the first kPrHubs vertices
     uint32_t items = 0;
     int2 *d_item_info = nullptr;
     uint32_t *d_item_first = nullptr;

@@ -63,6 +63,37 @@ def test_pagerank_rmat22_full_size():
     np.testing.assert_allclose(got.cpu().numpy(), want, rtol=1e-11, atol=0)
 
 
+@pytest.mark.parametrize("degrees", [
+    [1, 2, 8, 9, 16, 17, 32, 33, 63, 64, 65], [511, 512, 513, 1024, 1025, 16 * 512 + 1, 70000],
+    [64] * 65, [65] * 5 + [8] * 127, [513] * 40,
+], ids=str)
+def test_pagerank_degree_edges(degrees):
+    """Degrees at the edges of the lanes per vertex, items and chunks, as in-
+    and as out-degrees (the other direction then has one arc a vertex)."""
+    h, leaves = len(degrees), max(degrees)
+    a = [(i, h + j) for i, d in enumerate(degrees) for j in range(d)]
+    for arcs in (a, [(v, u) for u, v in a]):
+        check(gg.directed(h + leaves, arcs, "edges"))
+
+
+@pytest.mark.parametrize("n", [20351, 20352, 20353])
+def test_pagerank_hubs_in_lds(n):
+    """Enough arcs that the shares of the first 20,352 vertices sit in LDS, at
+    one vertex fewer, all of them, and one more."""
+    rng = np.random.default_rng(n)
+    u, v = rng.integers(0, n, (2, 9 << 20))
+    u[:n] = np.arange(n)  # no vertex without out-arcs but the last
+    check(gg.directed(n, np.stack([u, v], 1)[u != n - 1], "dense"))
+
+
+def check(g):
+    want, it_o, _ = oracle.pagerank(g.row_ptr, g.col_idx, 0.85, 0.0, 10)
+    with graph(g) as G:
+        got, it = G.pagerank(0.85, 0.0, 10)
+    assert it == it_o
+    np.testing.assert_allclose(got.cpu().numpy(), want, rtol=1e-11, atol=0)
+
+
 def test_pagerank_argument_errors():
     g = gg.path(4)
     with graph(g) as G:
