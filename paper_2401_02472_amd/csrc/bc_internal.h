@@ -354,9 +354,22 @@ hipError_t pair_sum(const PairDev &d, const int32_t *caller, double *out, bool c
 // Device view of a single-source shortest-path run (bc_sssp.hip): the graph's
 // out-arcs with their weights (NULL: every arc weighs 1), the same chunk items
 // as the batched BC path, a distance and a pass stamp per vertex.
+// What one pass leaves to the next: about the arcs of the pending vertices
+// (0: none pending) and INT32_MAX - their smallest distance, in kSsspSlots
+// slots of a cache line each (the atomics of 1,000 workgroups on one line took
+// 20 us of a pass).
+constexpr int kSsspSlots = 64;
+struct SsspSlot {
+    unsigned long long work;
+    uint32_t key, pad[29];
+};
 struct SsspDev {
     int32_t n;
-    int32_t big_end;
+    int32_t big_end, multi_end, mid_end, live_end;
+    // a pass with more than `split` pending arcs takes only the distances
+    // within delta of the smallest (-1: every pass takes all)
+    int64_t split;
+    int32_t delta;
     uint32_t items;
     const int32_t *row_ptr;
     const int32_t *col_idx;
@@ -398,8 +411,8 @@ hipError_t pagerank_init(const PrDev &d, int32_t max_iter, hipStream_t stream);
 hipError_t pagerank_pull(const PrDev &d, int32_t iter, hipStream_t stream);
 hipError_t pagerank_finish(const PrDev &d, int32_t iter, hipStream_t stream);
 
-hipError_t sssp_init(int32_t n, int32_t *dist, int32_t *stamp, int32_t src, hipStream_t stream);
-hipError_t sssp_pass(const SsspDev &d, int32_t pass, const int32_t *prev, int32_t *cur,
+hipError_t sssp_init(const SsspDev &d, int32_t src, SsspSlot *left, hipStream_t stream);
+hipError_t sssp_pass(const SsspDev &d, int32_t pass, SsspSlot *left, int32_t *quiet,
                      hipStream_t stream);
 hipError_t sssp_export(int32_t n, const int32_t *perm, const int32_t *dist, int32_t *out,
                        hipStream_t stream);

@@ -5,6 +5,23 @@
 
 using namespace bcx;
 
+namespace {
+
+// Distances that a pass with much to do takes at once.  A relaxed vertex
+// improves neighbours by up to the largest weight, the smallest of d of them
+// by 1/d of that, d the degree at the end of an arc: four such steps on
+// uniform graphs (16M arcs, weights to 100: 25 takes 29 passes and 1.08 times
+// every arc, 6 takes 51, 50 relaxes 1.37 times), and no less than 1/48 of it,
+// as where hubs make d thousands (31M-arc R-MAT: 2 takes 18 passes and 1.00
+// times every arc, 4 takes 16 and 1.28, 16 takes 11 and 2.0).
+int32_t sssp_delta(const bc_graph_s *g) {
+    const double top = g->d_weight ? g->max_weight : 1;
+    const double delta = std::max(4.0 * top / std::max(g->arc_degree, 1.0), top / 48.0);
+    return (int32_t)std::min(std::max(delta, 1.0), 1e9);
+}
+
+}  // namespace
+
 extern "C" {
 
 bc_status bc_set_weights(bc_graph_t g, const int32_t *weight) {
@@ -47,6 +64,7 @@ bc_status bc_set_weights(bc_graph_t g, const int32_t *weight) {
     }
     if (g->d_weight) (void)hipFree(g->d_weight);
     g->d_weight = w_new;
+    g->max_weight = maxw;
     return BC_OK;
 }
 
@@ -56,18 +74,22 @@ bc_status bc_sssp(bc_graph_t g, int32_t source, int32_t *dist_dev, void *stream_
     std::lock_guard<std::mutex> lk(g->sssp_mu);
     const hipStream_t stream = (hipStream_t)stream_;
     auto &w = g->sssp;
-    constexpr int32_t K = 8;  // passes queued per host poll
+    // passes queued per host poll: 8, 12, 18, ... 32 (a poll takes 40 us, about
+    // as much as 9 passes that find nothing to do)
+    constexpr int64_t kFirst = 8, kMost = 32;
     if (!w.dist) {
         hipError_t e = hipMalloc(&w.dist, (size_t)g->n * sizeof(int32_t));
         if (e == hipSuccess) e = hipMalloc(&w.stamp, (size_t)g->n * sizeof(int32_t));
-        if (e == hipSuccess) e = hipMalloc(&w.flags, 2 * K * sizeof(int32_t));
+        if (e == hipSuccess) e = hipMalloc(&w.flags, kMost * sizeof(int32_t));
+        if (e == hipSuccess) e = hipMalloc(&w.slots, 3 * kSsspSlots * sizeof(SsspSlot));
         if (e == hipSuccess) e = hipMalloc(&w.d_stats, kStatWords * sizeof(unsigned long long));
         if (e == hipSuccess)
-            e = hipHostMalloc((void **)&w.h_flags, K * sizeof(int32_t), hipHostMallocDefault);
+            e = hipHostMalloc((void **)&w.h_flags, kMost * sizeof(int32_t), hipHostMallocDefault);
         if (e != hipSuccess) {
             if (w.dist) (void)hipFree(w.dist);
             if (w.stamp) (void)hipFree(w.stamp);
             if (w.flags) (void)hipFree(w.flags);
+            if (w.slots) (void)hipFree(w.slots);
             if (w.d_stats) (void)hipFree(w.d_stats);
             w = bc_graph_s::Sssp{};
             return from_hip(e);
@@ -79,6 +101,17 @@ bc_status bc_sssp(bc_graph_t g, int32_t source, int32_t *dist_dev, void *stream_
     SsspDev d{};
     d.n = g->n;
     d.big_end = g->big_end;
+    d.multi_end = g->multi_end;
+    d.mid_end = g->mid_end;
+    d.live_end = g->live_end;
+    d.delta = sssp_delta(g);
+    // About the arcs that take as long as one more pass.  Where all arcs are
+    // not much more than that, no pass chooses and none keeps the books for it
+    // (ms with / without the choice: 262K-vertex R-MAT 0.44 / 0.68, 65K 0.33 /
+    // 0.47, uniform random 200K vertices 0.53 / 0.81, 2M 1.5 / 3.0; of average
+    // degree 4 and 300K vertices 0.57 / 0.50, a 1M-vertex grid 2.3 / 1.4).
+    d.split = (1 << 20) + 2 * (int64_t)g->live_end;
+    if (2 * g->nnz < 3 * d.split) d.split = -1;
     d.items = g->items;
     d.row_ptr = g->d_row_ptr;
     d.col_idx = g->d_col_idx;
@@ -88,30 +121,29 @@ bc_status bc_sssp(bc_graph_t g, int32_t source, int32_t *dist_dev, void *stream_
     d.stamp = w.stamp;
     hipError_t e = hipSuccess;
     if (prof) e = hipMemsetAsync(w.d_stats, 0, kStatWords * sizeof(unsigned long long), stream);
-    if (e == hipSuccess) e = sssp_init(g->n, w.dist, w.stamp, g->h_perm[(size_t)source], stream);
-    // flag of pass p (1, 2, ...) in block ((p-1)/K) & 1; a block is cleared
-    // before its chunk of passes is queued
-    auto slot = [&](int32_t p) { return w.flags + (((p - 1) / K) & 1) * K + (p - 1) % K; };
+    if (e == hipSuccess) e = sssp_init(d, g->h_perm[(size_t)source], w.slots, stream);
     bool done = false;
-    for (int32_t p0 = 1; e == hipSuccess && !done; p0 += K) {
-        if (p0 > g->n + K) {  // more passes than a shortest path has arcs: cannot happen
+    for (int64_t p0 = 1, K = kFirst; e == hipSuccess && !done; p0 += K, K = std::min(K + K / 2, kMost)) {
+        // every pass takes the pending vertices of smallest distance, which is
+        // final: more passes than vertices cannot happen
+        if (p0 > (int64_t)g->n + kMost) {
             e = hipErrorUnknown;
             break;
         }
-        e = hipMemsetAsync(slot(p0), 0, K * sizeof(int32_t), stream);
-        for (int32_t p = p0; p < p0 + K && e == hipSuccess; ++p) {
+        e = hipMemsetAsync(w.flags, 0, K * sizeof(int32_t), stream);
+        for (int32_t p = (int32_t)p0; p < p0 + K && e == hipSuccess; ++p) {
             const bool m = prof && (p - 1) % stride == 0;
             timer.on = m;
             d.stats = m ? w.d_stats + 9 : nullptr;
             e = timer.begin(BC_PROF_SSSP, stream);
-            if (e == hipSuccess) e = sssp_pass(d, p, p == 1 ? nullptr : slot(p - 1), slot(p), stream);
+            if (e == hipSuccess) e = sssp_pass(d, p, w.slots, w.flags + (p - p0), stream);
             if (e == hipSuccess) e = timer.end(stream);
         }
         if (e == hipSuccess)
-            e = hipMemcpyAsync(w.h_flags, slot(p0), K * sizeof(int32_t), hipMemcpyDeviceToHost,
+            e = hipMemcpyAsync(w.h_flags, w.flags, K * sizeof(int32_t), hipMemcpyDeviceToHost,
                                stream);
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
-        for (int32_t q = 0; q < K && e == hipSuccess; ++q) done |= w.h_flags[q] == 0;
+        for (int32_t q = 0; q < K && e == hipSuccess; ++q) done |= w.h_flags[q] != 0;
     }
     if (e == hipSuccess) e = sssp_export(g->n, g->d_perm, w.dist, dist_dev, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);

@@ -92,6 +92,7 @@ void free_graph_arrays(bc_graph_s *g) {
     if (w.dist) (void)hipFree(w.dist);
     if (w.stamp) (void)hipFree(w.stamp);
     if (w.flags) (void)hipFree(w.flags);
+    if (w.slots) (void)hipFree(w.slots);
     if (w.h_flags) (void)hipHostFree(w.h_flags);
     if (w.d_stats) (void)hipFree(w.d_stats);
     w = bc_graph_s::Sssp{};
@@ -282,9 +283,11 @@ bc_status bc_create_graph(int32_t n, const int32_t *row_ptr, const int32_t *col_
     while (g->mid_end < n && key_deg(iperm[(size_t)g->mid_end]) > kB0MaxDeg) ++g->mid_end;
     std::vector<int32_t> new_rp((size_t)n + 1, 0), new_rp_in;
     if (directed) new_rp_in.assign((size_t)n + 1, 0);
+    double squares = 0;
     for (int32_t u = 0; u < n; ++u) {
         const int32_t o = iperm[(size_t)u];
         const int32_t dgr = out_deg(o);
+        squares += (double)dgr * key_deg(o);
         new_rp[(size_t)u + 1] = new_rp[(size_t)u] + dgr;
         if (directed) new_rp_in[(size_t)u + 1] = new_rp_in[(size_t)u] + in_deg(o);
         // one-source path buckets (id ranges; undirected graphs only run there,
@@ -294,6 +297,9 @@ bc_status bc_create_graph(int32_t n, const int32_t *row_ptr, const int32_t *col_
         if (b >= 2) g->b2_end = u + 1;
         if (b >= 1) g->b1_end = u + 1;
     }
+    g->live_end = n;
+    while (g->live_end > 0 && key_deg(iperm[(size_t)g->live_end - 1]) == 0) --g->live_end;
+    if (nnz > 0) g->arc_degree = squares / (double)nnz;
     g->hub_arcs = new_rp[(size_t)std::min(n, kPrHubs)];
     uint64_t chunks = 0;
     for (int32_t u = 0; u < g->b3_end; ++u) chunks += chunks_of(out_deg(iperm[(size_t)u]));

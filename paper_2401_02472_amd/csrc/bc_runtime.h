@@ -223,6 +223,8 @@ struct bc_graph_s {
     int32_t mid_end = 0;  // vertices of key degree > 8 (a prefix)
     int32_t max_deg = 0;  // largest key degree
     int64_t hub_arcs = 0;  // arcs out of the first kPrHubs vertices
+    int32_t live_end = 0;  // vertices with an arc (a prefix)
+    double arc_degree = 0;  // mean key degree of the vertex that an arc leaves
     uint32_t items = 0;
     int2 *d_item_info = nullptr;
     uint32_t *d_item_first = nullptr;
@@ -257,10 +259,13 @@ struct bc_graph_s {
     // single-source shortest paths: arc weights (internal arc order; NULL =
     // every arc weighs 1) and a workspace used by one call at a time
     int32_t *d_weight = nullptr;
+    int32_t max_weight = 1;
     std::mutex sssp_mu;
     struct Sssp {
-        int32_t *dist = nullptr, *stamp = nullptr, *flags = nullptr;
-        int32_t *h_flags = nullptr;               // pinned mirror of one flag block
+        int32_t *dist = nullptr, *stamp = nullptr;
+        int32_t *flags = nullptr;                 // per queued pass: it found nothing pending
+        bcx::SsspSlot *slots = nullptr;
+        int32_t *h_flags = nullptr;               // pinned mirror of the flags
         unsigned long long *d_stats = nullptr;    // kStatWords counters ([9..11] used)
     } sssp;
     // PageRank workspace (one call at a time)

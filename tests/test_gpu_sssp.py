@@ -58,6 +58,29 @@ def test_sssp_unit_weights_without_set_weights_and_zero_weights():
             assert np.array_equal(gpu_dist(G, s), want)
 
 
+@pytest.mark.parametrize("lo,hi", [(1, 100), (0, 3), (1, 1), (1, 14000)])
+@pytest.mark.parametrize("g", [
+    gg.erdos_renyi(150_000, 16, seed=3), gg.rmat(17, 16, seed=6),
+    gg.rmat(17, 16, seed=6, directed=True),
+], ids=lambda g: g.name)
+def test_sssp_passes_by_distance(g, lo, hi):
+    """Enough arcs that a pass takes only the nearest pending vertices."""
+    w = gg.edge_weights(g, seed=7, lo=lo, hi=hi)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx, flags=flags_of(g)) as G:
+        G.set_weights(w)
+        for s in gg.sample_sources(g, 2, seed=8):
+            want, _ = oracle.sssp(g.row_ptr, g.col_idx, w, int(s))
+            assert np.array_equal(gpu_dist(G, s), want)
+
+
+def test_sssp_largest_distance():
+    """The arc back from the farthest vertex would pass the range of int32."""
+    g = gg.path(3)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        G.set_weights(np.full(4, (1 << 30) - 1, np.int32))
+        assert gpu_dist(G, 0).tolist() == [0, (1 << 30) - 1, (1 << 31) - 2]
+
+
 def test_sssp_weight_errors():
     g = gg.path(3)
     with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
