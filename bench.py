@@ -753,8 +753,12 @@ def main() -> int:
         else:
             cls = max(("forward", "reverse"), key=lambda c: prof[c]["ms"])
             pc = prof[cls]
-            alg_bytes = sum(BYTES[(path, cls)][u] * pc[u] for u in BYTES[(path, cls)])
-            kernel_name = KERNELS[(path, cls)]
+            # the queues of deep graphs examine no group of vertices: a vertex
+            # of one source at a time, as the one-source path
+            pairs = path == "batched" and prof["forward"]["vertices"] == 0
+            model = BYTES[("plain" if pairs else path, cls)]
+            alg_bytes = sum(model[u] * pc[u] for u in model)
+            kernel_name = f"k_pair_{cls}" if pairs else KERNELS[(path, cls)]
         launches = max(pc["launches"], 1)
         avg_ms = pc["ms"] / launches
         per_launch = alg_bytes / launches

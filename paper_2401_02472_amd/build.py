@@ -10,10 +10,10 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libbc_mi355x.so")
 # the same library with the cross-lane exec checks compiled in (BC_CHECK_EXEC)
 CHECK_LIB_PATH = os.path.join(HERE, "libbc_mi355x_check.so")
-SOURCES = ["bc_graph.hip", "bc_plain.hip", "bc_batched.hip", "bc_source.hip", "bc_pair.hip", "bc_layout.hip", "bc_sssp.hip",
-           "bc_pagerank.hip", "bc_rt_graph.hip", "bc_rt_plain.hip", "bc_rt_batched.hip",
-           "bc_rt_source.hip", "bc_rt_pair.hip", "bc_rt_algos.hip", "bc_tune.hip",
-           "bc_capi.hip", "bc_noalloc.hip"]
+SOURCES = ["bc_graph.hip", "bc_plain.hip", "bc_batched.hip", "bc_source.hip", "bc_pair.hip",
+           "bc_layout.hip", "bc_sssp.hip", "bc_pagerank.hip", "bc_rt_graph.hip",
+           "bc_rt_plain.hip", "bc_rt_batched.hip", "bc_rt_source.hip", "bc_rt_pair.hip",
+           "bc_rt_algos.hip", "bc_tune.hip", "bc_capi.hip", "bc_noalloc.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
