@@ -74,10 +74,14 @@ struct Work {
 template <bool FWD>
 __device__ __forceinline__ void arc_batch(const LevelCtx &c, int32_t first, int32_t stride,
                                           int32_t count, double &acc, Work &wk) {
+    // (through the caches: the other pass and the next source read the ids
+    // again, out of the last-level cache where they fit its 256 MB.  Loads that
+    // bypass it made the heaviest level of the scale-20 R-MAT 118 us, now 86,
+    // and eight sources at scale 22, 513 MB of ids, 16.8 ms, now 15.6.)
     int32_t v[kBatch];
 #pragma unroll
     for (int j = 0; j < kBatch; ++j)
-        v[j] = (j < count) ? __builtin_nontemporal_load(&c.d.col_idx[first + stride * j]) : -1;
+        v[j] = (j < count) ? c.d.col_idx[first + stride * j] : -1;
     uint32_t code[kBatch];
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) code[j] = (v[j] >= 0) ? lev_code(c.d.lev3, v[j]) : 4u;
@@ -293,6 +297,11 @@ __global__ __launch_bounds__(kBlock) void k_level(PlainDev d, int32_t L, int32_t
 // are cleared.  Thread t owns vertices 16t .. 16t+15 (one code word, one
 // 16-byte mark group), so codes are written without atomics.  The kernel also
 // completes the sigma of the level-L bucket-3 vertices.
+//
+// Bound by the atomics on one line (about 5 ns each): queue positions are taken
+// once per workgroup and bucket, and the depth is a plain store (with one atomic
+// per wave and bucket, and two for the depth, 12 to 21 us of a dense level of
+// the scale-20 R-MAT; now 9 to 10).
 __global__ __launch_bounds__(kBlock) void k_compact(PlainDev d, int32_t L, int32_t last,
                                                     int32_t *trunc_flag) {
     const LevelRec cur = d.lvl[L];
@@ -329,15 +338,16 @@ __global__ __launch_bounds__(kBlock) void k_compact(PlainDev d, int32_t L, int32
     const int32_t words = (d.n + 15) >> 4;
     LevelRec *nx = &d.lvl[L + 1];
     const int lane = lane_id();
-    // All lanes of a wave run the same number of iterations (ballots inside).
+    __shared__ uint32_t s_tot[kWavesPerBlock][5], s_base[5];
+    const int wv_id = (int)threadIdx.x / kWave;
+    // All threads of a workgroup run the same number of iterations (barriers inside).
     const int32_t stride = gridDim.x * kBlock;
-    const int32_t base0 = blockIdx.x * kBlock + (threadIdx.x & ~(kWave - 1));
-    for (int32_t wb = base0; wb < words; wb += stride) {
-        const int32_t i = wb + lane;
+    for (int32_t wb = blockIdx.x * kBlock; wb < words; wb += stride) {
+        const int32_t i = wb + (int32_t)threadIdx.x;
         uint4 m = make_uint4(0u, 0u, 0u, 0u);
         if (i < words) m = reinterpret_cast<const uint4 *>(d.nextmap)[i];
         const bool any = (m.x | m.y | m.z | m.w) != 0u;
-        if (__ballot(any) == 0) continue;
+        if (!__syncthreads_or(any)) continue;
         uint32_t bits = 0;  // bit j: vertex 16i+j is marked
         {
             const uint32_t wv[4] = {m.x, m.y, m.z, m.w};
@@ -381,31 +391,46 @@ __global__ __launch_bounds__(kBlock) void k_compact(PlainDev d, int32_t L, int32
 #pragma unroll
         for (int b = 0; b < 4; ++b) off[b] = wave_excl_scan(cb[b], tot[b]);
         offc3 = wave_excl_scan(ch3, totc3);
-        uint32_t base[4] = {0u, 0u, 0u, 0u}, basec3 = 0u;
         if (lane == 0) {
 #pragma unroll
-            for (int b = 0; b < 3; ++b)
-                if (tot[b]) base[b] = atomicAdd(&nx->cnt[b], tot[b]);
-            if (tot[3]) {
-                const unsigned long long old = atomicAdd(
-                    &nx->cnt3, ((unsigned long long)tot[3] << 32) | (unsigned long long)totc3);
-                base[3] = (uint32_t)(old >> 32);
-                basec3 = (uint32_t)(old & 0xffffffffu);
+            for (int b = 0; b < 4; ++b) s_tot[wv_id][b] = tot[b];
+            s_tot[wv_id][4] = totc3;
+        }
+        __syncthreads();
+        if (threadIdx.x < 4) {  // thread b: bucket b of the workgroup
+            uint32_t t = 0, tc = 0;
+            for (int w = 0; w < kWavesPerBlock; ++w) {
+                t += s_tot[w][threadIdx.x];
+                tc += s_tot[w][4];
             }
-            const uint32_t found = tot[0] + tot[1] + tot[2] + tot[3];
-            if (found) {
-                atomicMax(&d.ctrl[0], L + 1);
-                atomicMax(&d.ctrl[3], L + 1);
+            if (threadIdx.x < 3) {
+                s_base[threadIdx.x] = t ? atomicAdd(&nx->cnt[threadIdx.x], t) : 0u;
+            } else {
+                const unsigned long long old =
+                    t ? atomicAdd(&nx->cnt3, ((unsigned long long)t << 32) | tc) : 0ull;
+                s_base[3] = (uint32_t)(old >> 32);
+                s_base[4] = (uint32_t)old;
+            }
+            if (t) {
+                // every writer of this launch stores the same values
+                d.ctrl[0] = L + 1;
+                if (d.ctrl[3] < L + 1) d.ctrl[3] = L + 1;
                 if (L == last) {  // more levels than were launched for this source
-                    atomicOr(&d.ctrl[2], 1);
-                    if (trunc_flag) atomicOr(trunc_flag, 1);
+                    d.ctrl[2] = 1;
+                    if (trunc_flag) *trunc_flag = 1;
                 }
-                if (d.stats) atomicAdd(&d.stats[3], (unsigned long long)found);
+                if (d.stats) atomicAdd(&d.stats[3], (unsigned long long)t);
             }
         }
+        __syncthreads();
+        uint32_t base[4], basec3 = s_base[4];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) base[b] = __shfl(base[b], 0);
-        basec3 = __shfl(basec3, 0);
+        for (int b = 0; b < 4; ++b) base[b] = s_base[b];
+        for (int w = 0; w < wv_id; ++w) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) base[b] += s_tot[w][b];
+            basec3 += s_tot[w][4];
+        }
         if (bits) {
             uint32_t p0 = ns[0] + base[0] + off[0], p1 = ns[1] + base[1] + off[1];
             uint32_t p2 = ns[2] + base[2] + off[2], p3 = nv3 + base[3] + off[3];

@@ -191,3 +191,19 @@ def test_road_grid_without_shortcuts_range():
             assert np.array_equal(dist, od)
             far = osg < 1e300
             check_sigma(sigma[far], osg[far])
+
+
+@pytest.mark.parametrize("n", [255, 4095, 4096, 4097, 8193, 70001])
+def test_level_queues_across_workgroups(n):
+    """One level with vertices of every degree class, at vertex counts around
+    the 4,096 that a workgroup of the queue step looks at."""
+    rng = np.random.default_rng(n)
+    src = np.arange(1, n)
+    hubs = [(h, int(v)) for h, d in ((1, min(3000, n // 2)), (2, 70), (3, 9))
+            for v in rng.choice(np.arange(4, n), min(d, n - 4), replace=False)]
+    u = np.concatenate([np.zeros(n - 1, int), [h for h, _ in hubs]])
+    v = np.concatenate([src, [x for _, x in hubs]])
+    g = gg.csr_from_edges(n, u, v)
+    s = np.array([0, 1, 3, n - 1], np.int32)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        check_bc(plain(G, s), oracle_bc(g, s))
