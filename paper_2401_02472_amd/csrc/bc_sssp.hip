@@ -300,7 +300,10 @@ __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d,
             }
         }
     }
-    if (d.stats) {
+    if (d.stats) {  // one atomic per workgroup and counter: they share a line
+        __shared__ unsigned long long s_stats[3];
+        if (threadIdx.x < 3) s_stats[threadIdx.x] = 0;
+        __syncthreads();
         unsigned long long a = r.active, b = r.arcs, c = r.better;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
@@ -309,10 +312,13 @@ __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d,
             c += __shfl_xor(c, off);
         }
         if (lane == 0 && (a | b | c)) {
-            atomicAdd(&d.stats[0], a);
-            atomicAdd(&d.stats[1], b);
-            atomicAdd(&d.stats[2], c);
+            atomicAdd(&s_stats[0], a);
+            atomicAdd(&s_stats[1], b);
+            atomicAdd(&s_stats[2], c);
         }
+        __syncthreads();
+        if (threadIdx.x < 3 && s_stats[threadIdx.x])
+            atomicAdd(&d.stats[threadIdx.x], s_stats[threadIdx.x]);
     }
 }
 
