@@ -38,8 +38,7 @@ static size_t pair_source_bytes(const bc_graph_s *g, const PairShape &sh) {
 }
 
 static size_t pair_ws_bytes(const bc_graph_s *g, int32_t k, const PairShape &sh) {
-    return (size_t)k * pair_source_bytes(g, sh) + 12 * kAlign +
-           kStatWords * sizeof(unsigned long long);
+    return (size_t)k * pair_source_bytes(g, sh) + 12 * kAlign;
 }
 
 static PairShape pair_shape(const bc_graph_s *g, int32_t k) {
@@ -78,6 +77,7 @@ size_t pair_bytes(const bc_graph_s *g, int32_t k) {
 void pair_ws_destroy(PairWS *ws) {
     if (!ws) return;
     ws->timer.destroy();
+    if (ws->d_stats) (void)hipFree(ws->d_stats);
     if (ws->block) (void)hipFree(ws->block);
     if (ws->h_depth) (void)hipHostFree(ws->h_depth);
     delete ws;
@@ -129,7 +129,6 @@ static bc_status pair_room(bc_graph_s *g, PairWS *ws, int32_t k, const PairShape
     d.range = d.depth + k;
     d.src = (int32_t *)take((size_t)k * sizeof(int32_t));
     d.at = (int32_t *)take((size_t)k * sizeof(int32_t));
-    ws->d_stats = (unsigned long long *)take(kStatWords * sizeof(unsigned long long));
     return BC_OK;
 }
 
@@ -302,7 +301,13 @@ bc_status pair_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_
     ws->timer.on = false;
     ws->timer.used = 0;
     hipError_t e = hipSuccess;
-    bool clear_stats = prof;
+    // the counters of every round of the call, those run again included (not in
+    // the block, which each round cuts anew)
+    if (prof) {
+        if (!ws->d_stats)
+            BC_TRY_HIP(hipMalloc(&ws->d_stats, kStatWords * sizeof(unsigned long long)));
+        BC_TRY_HIP(hipMemsetAsync(ws->d_stats, 0, kStatWords * sizeof(unsigned long long), stream));
+    }
     int32_t run_depth = 0;
     int64_t level_steps = 0;
     for (int32_t s0 = 0; s0 < k;) {
@@ -310,10 +315,6 @@ bc_status pair_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_
         st = pair_room(g, ws, m, sh);
         if (st != BC_OK) return st;
         PairDev &d = ws->dev;
-        if (clear_stats) {
-            BC_TRY_HIP(hipMemsetAsync(ws->d_stats, 0, kStatWords * sizeof(unsigned long long), stream));
-            clear_stats = false;
-        }
         int32_t *h_src = ws->h_depth + m + 1;
         for (int32_t i = 0; i < m; ++i) h_src[i] = g->h_perm[(size_t)sources[s0 + i]];
         e = hipMemcpyAsync((void *)d.src, h_src, (size_t)m * sizeof(int32_t), hipMemcpyHostToDevice,

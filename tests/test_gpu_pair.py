@@ -90,6 +90,45 @@ def test_profiled_run_counts_the_pairs():
         assert p["reverse"]["hits"] == p["forward"]["hits"] - first
 
 
+@pytest.mark.parametrize("case", ["rounds", "range", "grow"])
+def test_profiled_run_of_several_rounds(case):
+    """The counters hold every round of a call: rounds of unequal size, sources
+    run again with exponents, sources run again with room for more levels."""
+    if case == "rounds":  # 3.4 MB of scratch per source, 4 GB per round
+        g = gg.grid_road(400, 400, seed=10)
+        src = np.tile(gg.sample_sources(g, 13, seed=11), 100)
+    elif case == "range":
+        g = gg.grid_full(600, 600)
+        src = np.array([0, 599, 180300, 359999], np.int32)
+    else:
+        g = gg.path(21000)
+        src = np.array([0, 20999, 10000, 3], np.int32)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        plain(G, src[:1])  # found deep; the pair path has not run yet
+        G.profile_enable(True)
+        G.profile_read(reset=True)
+        batched(G, src)
+        p = G.profile_read(reset=True)
+        pairs = src.size * g.n  # the graphs are connected but for a few vertices
+        assert p["forward"]["vertices"] == 0, "not the pair path"
+        if case == "rounds":
+            _, dist, _ = G.run_detail(src[:13], bcm.make_options(bcm.BC_MODE_BATCHED))
+            pairs = 100 * int((dist >= 0).sum())
+            assert p["forward"]["owners"] == pairs
+            assert p["reverse"]["owners"] == pairs - src.size
+        else:
+            # a round that is given up counts what it did: one without
+            # exponents, five with 1024 << i of the path's 21,000 levels
+            tries = 2 if case == "range" else 6
+            assert pairs <= p["forward"]["owners"] <= tries * pairs
+            assert pairs - src.size <= p["reverse"]["owners"] <= tries * pairs
+            assert p["forward"]["owners"] <= p["forward"]["arcs"] + 2 * src.size
+            batched(G, src)  # one round
+            p = G.profile_read(reset=True)
+            assert p["forward"]["owners"] == pairs
+            assert p["reverse"]["owners"] == pairs - src.size
+
+
 def test_counts_beyond_double_range():
     """A lattice whose counts pass double's range: found on the way, run again
     with exponents, and with them from the start in later calls."""
