@@ -123,10 +123,10 @@ typedef struct bc_options {
  * and polling costs dominate.  A source's values must fit a compute unit's
  * LDS: graphs of more than 20,415 vertices take HOST.  AUTO picks the loop
  * with the lower estimated time for the call's source count; an undirected
- * graph of at most 16 arcs per vertex and 8 on average, once a run has found
- * it deep (more than 48 levels), takes per-source queues instead, a launch per
- * level or a workgroup per source (extended range included; the graph keeps a
- * copy of its arcs in an order for that).  Otherwise a graph in extended range
+ * graph of at most 16 arcs per vertex and 8 on average that is deep (more than
+ * 48 levels from one of four vertices) takes per-source queues instead, a
+ * launch per level or a workgroup per source (extended range included; the
+ * graph keeps a copy of its arcs in an order for that).  Otherwise a graph in extended range
  * always takes HOST (or GRAPH).  GRAPH:
  * the HOST loop with each chunk of level steps (the levels between two depth
  * polls, forward and reverse) captured once per workspace as a HIP graph and

@@ -24,7 +24,7 @@ bool use_batched(const bc_graph_s *g, const bc_options *opt, int32_t k) {
     if (k >= g->tuned_min_batched.load()) return true;
     const int32_t loop = opt ? opt->level_loop : BC_LOOP_AUTO;
     const int32_t width = batch_width_of(g, opt, k);
-    // a graph found deep: every source's level steps together
+    // a deep graph: every source's level steps together
     if (use_pair(g, loop, width)) return true;
     // few sources: a workgroup per source (a batched loop) against the
     // one-source path, which spreads each source over the device

@@ -32,6 +32,48 @@ __global__ __launch_bounds__(kBlock) void k_gather(int32_t n, const int32_t *per
         dst[o] = src[perm[o]];
 }
 
+// Four breadth-first searches at once, a byte each of a vertex's word: 0 not
+// reached, else level + 1.
+__global__ __launch_bounds__(kBlock) void k_probe_seed(int32_t n, int32_t live, int32_t steps,
+                                                       uint32_t *word, int32_t *found) {
+    const int32_t at = blockIdx.x * blockDim.x + threadIdx.x, all = gridDim.x * blockDim.x;
+    for (int32_t v = at; v < n; v += all) {
+        uint32_t x = 0;
+        for (int j = 0; j < 4; ++j)
+            if (v == (int32_t)((int64_t)live * j / 4)) x |= 1u << (8 * j);
+        word[v] = x;
+    }
+    for (int32_t i = at; i < steps; i += all) found[i] = 0;
+}
+
+// Level L + 1 of the four: a vertex takes it where a neighbour is at level L.
+// Only a vertex's own thread writes its word, and a value that appears while
+// others read it is no level L.
+__global__ __launch_bounds__(kBlock) void k_probe_step(int32_t n, int32_t L, const int32_t *rp,
+                                                       const int32_t *ci, uint32_t *word,
+                                                       int32_t *found) {
+    if (L > 0 && found[L - 1] == 0) return;
+    bool any = false;
+    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
+        const uint32_t mine = word[v];
+        uint32_t take = 0;
+        bool open = false;
+        for (int j = 0; j < 4; ++j) open |= (mine >> (8 * j) & 255u) == 0u;
+        if (!open) continue;
+        for (int32_t e = rp[v], re = rp[v + 1]; e < re; ++e) {
+            const uint32_t x = word[ci[e]];
+            for (int j = 0; j < 4; ++j)
+                if ((mine >> (8 * j) & 255u) == 0u && (x >> (8 * j) & 255u) == (uint32_t)L + 1u)
+                    take |= ((uint32_t)L + 2u) << (8 * j);
+        }
+        if (take) {
+            word[v] = mine | take;
+            any = true;
+        }
+    }
+    if (any) found[L] = 1;
+}
+
 int grid_for(int64_t items) {
     int64_t g = (items + kBlock - 1) / kBlock;
     return (int)(g < 1 ? 1 : (g > 4096 ? 4096 : g));
@@ -45,6 +87,17 @@ hipError_t relabel_csr(int32_t n, int64_t nnz, const int32_t *old_rp, const int3
     if (nnz == 0 || n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_relabel, dim3(grid_for(nnz)), dim3(kBlock), 0, stream, n, nnz, old_rp,
                        old_ci, new_rp, perm, iperm, new_ci);
+    return hipGetLastError();
+}
+
+hipError_t depth_probe(int32_t n, int32_t live, const int32_t *row_ptr, const int32_t *col_idx,
+                       int32_t steps, uint32_t *word, int32_t *found, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_probe_seed, dim3(grid_for(n)), dim3(kBlock), 0, stream, n, live, steps,
+                       word, found);
+    for (int32_t L = 0; L < steps; ++L)
+        hipLaunchKernelGGL(k_probe_step, dim3(grid_for(n)), dim3(kBlock), 0, stream, n, L, row_ptr,
+                           col_idx, word, found);
     return hipGetLastError();
 }
 

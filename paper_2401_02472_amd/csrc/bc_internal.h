@@ -297,6 +297,7 @@ hipError_t source_sum(const SourceSum *sums, int32_t nsums, int32_t max_n, hipSt
 // Brandes over (vertex, source) pairs (bc_pair.hip): one part's arrays, each
 // [k][stride] (stride: n rounded up to 16) unless noted.
 constexpr int kPairMaxDeg = 16;  // most arcs of a vertex on this path
+constexpr int kPairSum = 8;      // sources whose dependencies are added as one group
 
 struct PairGraph {
     const int32_t *row_ptr, *col_idx;  // in the pair path's vertex order
@@ -427,6 +428,11 @@ hipError_t permute_arc_values(int32_t n, int64_t nnz, const int32_t *old_rp,
 hipError_t relabel_csr(int32_t n, int64_t nnz, const int32_t *old_rp, const int32_t *old_ci,
                        const int32_t *new_rp, const int32_t *perm, const int32_t *iperm,
                        int32_t *new_ci, hipStream_t stream);
+// Breadth-first from the vertices live * j / 4 (j = 0 .. 3), `steps` levels of
+// an undirected graph: found[L] != 0 where one of them has a level L + 1.
+// word: [n] scratch.
+hipError_t depth_probe(int32_t n, int32_t live, const int32_t *row_ptr, const int32_t *col_idx,
+                       int32_t steps, uint32_t *word, int32_t *found, hipStream_t stream);
 // dst[o] = src[perm[o]] for o < n (internal order -> caller order).
 hipError_t gather_f64(int32_t n, const int32_t *perm, const double *src, double *dst,
                       hipStream_t stream);

@@ -41,6 +41,10 @@ namespace bcx {
 namespace {
 
 constexpr int kPairFlight = 4;  // arcs of a pair looked at together
+// Counts from here on take exponents.  Below the largest double, so that
+// (1 + delta) / sigma stays a normal number without them: a sum is then the
+// same to the bit with exponents and without.
+constexpr double kPairRange = 0x1p1000;
 
 struct PairWork {
     uint32_t owners = 0, arcs = 0, hits = 0;
@@ -232,7 +236,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_forward(PairDev d, int32_t L, i
                     E += k;
                 }
                 ex[v] = E;
-            } else if (!(acc <= 0x1.fffffffffffffp+1023)) {
+            } else if (!(acc <= kPairRange)) {
                 *d.range = 1;
             }
             val[v] = acc;
@@ -441,7 +445,7 @@ __global__ __launch_bounds__(kDeepBlock) void k_deep_forward(PairDev d) {
                         E += k;
                     }
                     ex[v] = E;
-                } else if (!(acc <= 0x1.fffffffffffffp+1023)) {
+                } else if (!(acc <= kPairRange)) {
                     *d.range = 1;
                 }
                 val[v] = -par * acc;
@@ -588,14 +592,15 @@ __global__ void k_pair_seed(PairDev d) {
     d.depth[s] = 0;
 }
 
-// out[caller id] (+)= the sources' dependencies on each vertex: eight at a
-// time by a tree, the groups added in order.
-constexpr int kPairSum = 8;
+// out[caller id] (+)= the sources' dependencies on each vertex: kPairSum at a
+// time by a tree, the groups added in order (a later round's to the earlier
+// rounds' sum one by one, as if they were one round's).
 __global__ __launch_bounds__(kBlock) void k_pair_sum(PairDev d, const int32_t *caller, double *out,
                                                      int32_t carry) {
     const int32_t v = blockIdx.x * kBlock + threadIdx.x;
     if (v >= d.n) return;
-    double sum = 0.0;
+    const int32_t o = caller[v];
+    double sum = carry ? out[o] : 0.0;
     for (int32_t s0 = 0; s0 < d.k; s0 += kPairSum) {
         int c[kPairSum];
         double x[kPairSum];
@@ -613,8 +618,7 @@ __global__ __launch_bounds__(kBlock) void k_pair_sum(PairDev d, const int32_t *c
             for (int j = 0; j < w; ++j) x[j] += x[j + w];
         sum += x[0];
     }
-    const int32_t o = caller[v];
-    out[o] = carry ? out[o] + sum : sum;
+    out[o] = sum;
 }
 
 }  // namespace

@@ -285,7 +285,7 @@ hipError_t ChunkGraphs::replay(const BatchDev &d, int32_t dir, int32_t K, int32_
 hipError_t drive_batch(bc_graph_s *g, BatchDev &d, const ExtTables &ext, const int32_t *lanes_dev,
                        int32_t nl, int32_t *h_ctrl, hipStream_t stream, LaunchTimer &timer,
                        unsigned long long *d_stats, int32_t stride, BatchOutcome &how,
-                       int32_t &deepest, ChunkGraphs *cg, bool wide_ok, bool deep_ok) {
+                       int32_t &deepest, ChunkGraphs *cg, bool wide_ok) {
     const int32_t n = g->n;
     const bool prof = d_stats != nullptr;
     auto measure = [&](int32_t L) {
@@ -345,11 +345,6 @@ hipError_t drive_batch(bc_graph_s *g, BatchDev &d, const ExtTables &ext, const i
             return hipSuccess;
         }
         if (deepest < Lend || Lend >= n) break;
-        if (deep_ok && Lend > kPairDepth) {
-            g->deep.store(true);
-            how = BatchOutcome::Deep;
-            return hipSuccess;
-        }
         L0 = Lend;
     }
     if (cg) {
@@ -387,15 +382,13 @@ struct BatchPlan {
 // nseg == 0 everywhere, BC accumulates in the workspace and is gathered into
 // bc_out (caller order); otherwise each segment's output (caller order,
 // zeroed by the caller) receives its lanes' dependencies.  export_row maps a
-// lane of the run to the dist / sigma export row (or NULL: no export).  With
-// `deep`, a batch that finds the graph deep ends the plan: *deep is set and
-// the outputs mean nothing.
+// lane of the run to the dist / sigma export row (or NULL: no export).
 bc_status run_batch_plan(bc_graph_s *g, const std::vector<int32_t> &s_int,
                          const std::vector<BatchPlan> &plan,
                          const std::vector<int32_t> &seg_start,  // per segment table: nseg+1
                          const std::vector<double *> &seg_out, double *bc_out,
                          hipStream_t stream, const int32_t *export_row, int32_t *dist,
-                         double *sigma, int32_t sparse_div, bool graphs, bool *deep = nullptr) {
+                         double *sigma, int32_t sparse_div, bool graphs) {
     // two lane words per vertex when a batch has more than 64 sources (never
     // with request segments: their lanes are summed within one 64-lane word)
     int32_t H = 1;
@@ -486,21 +479,16 @@ bc_status run_batch_plan(bc_graph_s *g, const std::vector<int32_t> &s_int,
         // (measured runs launch every step: the events go around each launch)
         e = drive_batch(g, d, ext, d_lanes + bp.first, nl, ws->h_ctrl, stream, ws->timer,
                         prof ? ws->d_stats : nullptr, stride, how, deepest,
-                        graphs && !prof ? &ws->graphs : nullptr, ws->wide, deep != nullptr);
+                        graphs && !prof ? &ws->graphs : nullptr, ws->wide);
         if (e != hipSuccess) return fail(from_hip(e));
         if (how == BatchOutcome::NeedWide) {  // double rows from now on
             st = batch_widen(g, ws);
             if (st != BC_OK) return fail(st);
             continue;
         }
-        if (how == BatchOutcome::Deep) {
-            *deep = true;
-            return fail(BC_OK);
-        }
         if (how == BatchOutcome::Rerun) continue;
         if (how == BatchOutcome::Grow) {  // level array full: grow it, run the batch again
-            // (for a graph that may turn out deep, up to where that shows)
-            st = batch_grow_levels(g, ws, std::max(ws->lcap * 2, deep ? kPairDepth + 20 : 0));
+            st = batch_grow_levels(g, ws, ws->lcap * 2);
             if (st != BC_OK) return fail(st);
             continue;
         }
@@ -672,8 +660,6 @@ bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *
     }
     const bool state = dist || sigma;  // per-source exports: not on the pair path
     if (!state && use_pair(g, level_loop, width)) return pair_run(g, sources, k, bc_out, stream);
-    // a batch may find the graph deep, and the call starts over as pairs
-    const bool may_pair = !state && level_loop == BC_LOOP_AUTO && width <= kWave && pair_fits(g);
     std::vector<int32_t> order, s_int;
     std::vector<BatchPlan> plan;
     {
@@ -681,13 +667,9 @@ bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *
         if (st0 != BC_OK) return st0;
     }
     const int32_t P = parts_of(g, concurrency, (int32_t)plan.size(), width > kWave ? 2 : 1);
-    if (P <= 1) {
-        bool deep = false;
-        const bc_status st1 =
-            run_batch_plan(g, s_int, plan, {}, {}, bc_out, stream, order.data(), dist, sigma,
-                           sparse_div, level_loop == BC_LOOP_GRAPH, may_pair ? &deep : nullptr);
-        return deep ? pair_run(g, sources, k, bc_out, stream) : st1;
-    }
+    if (P <= 1)
+        return run_batch_plan(g, s_int, plan, {}, {}, bc_out, stream, order.data(), dist, sigma,
+                              sparse_div, level_loop == BC_LOOP_GRAPH);
     // P parts of consecutive batches, each on its own stream and workspace,
     // ordered after the caller's earlier work; BC = the parts' sum in part
     // order, on the caller's stream
@@ -716,19 +698,15 @@ bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *
     }
     const int32_t nb = (int32_t)plan.size();
     std::vector<bc_status> status((size_t)P, BC_OK);
-    std::vector<char> found_deep((size_t)P, 0);
     std::vector<std::thread> workers;
     for (int32_t i = 0; i < P; ++i) {
         workers.emplace_back([&, i]() {
             DeviceGuard dg(g->device);
             const int32_t b0 = (int32_t)((int64_t)nb * i / P), b1 = (int32_t)((int64_t)nb * (i + 1) / P);
             std::vector<BatchPlan> sub(plan.begin() + b0, plan.begin() + b1);
-            bool deep = false;
             status[(size_t)i] = run_batch_plan(g, s_int, sub, {}, {}, parts + (size_t)i * n,
                                                streams[(size_t)i], order.data(), dist, sigma,
-                                               sparse_div, level_loop == BC_LOOP_GRAPH,
-                                               may_pair ? &deep : nullptr);
-            found_deep[(size_t)i] = deep;
+                                               sparse_div, level_loop == BC_LOOP_GRAPH);
             if (hipEventRecord(ev_done[(size_t)i], streams[(size_t)i]) != hipSuccess &&
                 status[(size_t)i] == BC_OK)
                 status[(size_t)i] = BC_ERR_DEVICE;
@@ -749,8 +727,6 @@ bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     cleanup();
     if (e != hipSuccess) return from_hip(e);
-    if (std::count(found_deep.begin(), found_deep.end(), 1) > 0)
-        return pair_run(g, sources, k, bc_out, stream);
     return result;
 }
 

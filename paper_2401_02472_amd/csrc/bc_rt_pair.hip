@@ -14,9 +14,9 @@ bool pair_fits(const bc_graph_s *g) {
            g->nnz <= 8 * (int64_t)g->n;
 }
 
-// ... that a run has found deep (see kPairDepth).
+// ... that are deep (see kPairDepth).
 bool use_pair(const bc_graph_s *g, int32_t level_loop, int32_t width) {
-    return level_loop == BC_LOOP_AUTO && width <= kWave && pair_fits(g) && g->deep.load();
+    return level_loop == BC_LOOP_AUTO && width <= kWave && pair_fits(g) && g->deep;
 }
 
 static size_t pair_stride(const bc_graph_s *g) { return ((size_t)g->n + 15) & ~(size_t)15; }
@@ -63,10 +63,12 @@ static PairShape pair_shape(const bc_graph_s *g, int32_t k) {
     return sh;
 }
 
-// Sources run together of a call of k.
+// Sources run together of a call of k: whole groups of those that pair_sum
+// adds together, so that a call's sums are the same however many rounds its
+// shape (which follows the depth seen) makes of it.
 static int32_t pair_cap(const bc_graph_s *g, int32_t k, const PairShape &sh) {
-    const int64_t fit = (int64_t)(kPairBudget / pair_source_bytes(g, sh));
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(k, fit));
+    const int64_t fit = (int64_t)(kPairBudget / pair_source_bytes(g, sh)) / kPairSum * kPairSum;
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(k, std::max<int64_t>(fit, kPairSum)));
 }
 
 size_t pair_bytes(const bc_graph_s *g, int32_t k) {

@@ -314,7 +314,6 @@ bc_status plain_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc
     {
         // next run: launch two levels more than the deepest seen
         const int32_t seen = ws->h_ctrl[3] + 2;
-        if (seen > kPairDepth) g->deep.store(true);
         if (!polled && seen != g->depth_hint.load()) g->depth_hint.store(std::max(seen, 2));
     }
     if (prof) {

@@ -296,10 +296,11 @@ struct bc_graph_s {
     // set once a path count overflowed double: later batches keep level-scaled
     // counts (extended range, host-driven loop only)
     std::atomic<bool> sigma_ext{false};
-    // set once a batch ran deeper than kPairDepth levels: later calls take the
-    // pair path where the graph's degrees allow it, with exponents once a
-    // count passed double's range
-    std::atomic<bool> deep{false};
+    // more than kPairDepth levels, found at creation where the degrees allow the
+    // pair path (the choice is the graph's, not its calls', so that a call's
+    // result does not depend on the calls before it)
+    bool deep = false;
+    // pair-path runs keep exponents once a count passed double's range
     std::atomic<bool> pair_ext{false};
     // the pair path's vertex order and the CSR in it (built on first use)
     std::mutex layout_mu;
@@ -368,16 +369,15 @@ struct ExtTables {
 };
 // Rerun: run the batch again (the graph's rows became wider); Grow: with a
 // longer level array; NeedWide: the graph takes double rows and the
-// workspace's sigma rows are uint32-sized: widen them, then run the batch;
-// Deep: the graph is one for the pair path (only with `deep_ok`).
-enum class BatchOutcome { Done, Rerun, Grow, NeedWide, Deep };
+// workspace's sigma rows are uint32-sized: widen them, then run the batch.
+enum class BatchOutcome { Done, Rerun, Grow, NeedWide };
 // cg: replay the level chunks as captured graphs (NULL: launch every step).
 // wide_ok: d's sigma rows hold doubles (else uint32 only: a graph that takes
 // double rows gets NeedWide before anything is launched).
 hipError_t drive_batch(bc_graph_s *g, BatchDev &d, const ExtTables &ext, const int32_t *lanes_dev,
                        int32_t nl, int32_t *h_ctrl, hipStream_t stream, LaunchTimer &timer,
                        unsigned long long *d_stats, int32_t stride, BatchOutcome &how,
-                       int32_t &deepest, ChunkGraphs *cg, bool wide_ok, bool deep_ok = false);
+                       int32_t &deepest, ChunkGraphs *cg, bool wide_ok);
 
 // ---- one workgroup per source (bc_rt_source.hip) ----
 // One request of a job: sources [first, first + k) of its s_int, into out
@@ -407,8 +407,7 @@ bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
                       std::vector<char> &over);
 
 // ---- pairs (bc_rt_pair.hip) ----
-// A batch that is not finished after this many levels makes its graph a deep
-// one.
+// A graph with more levels than this (from one of four vertices) is a deep one.
 constexpr int32_t kPairDepth = 48;
 bool pair_fits(const bc_graph_s *g);
 bool use_pair(const bc_graph_s *g, int32_t level_loop, int32_t width);

@@ -167,6 +167,30 @@ def test_launch_per_level(rows, cols, short, k, ext):
         assert np.array_equal(got, batched(G, src))
 
 
+@pytest.mark.parametrize("g,k", [
+    (gg.grid_road(150, 150, seed=1), 1), (gg.grid_road(150, 150, seed=1), 3),
+    (gg.grid_road(150, 150, seed=1), 20), (gg.grid_road(400, 400, seed=10), 1300),
+    (_island_grid(), 3), (gg.grid_full(600, 600), 9),
+], ids=["k1", "k3", "k20", "rounds", "islands", "range"])
+def test_a_call_gives_the_same_bits_whatever_ran_before(g, k):
+    """The first call on a graph, one after calls with other sources, and one
+    on a graph that ran something else first (the rounds of the 1,300 sources
+    follow the depth seen)."""
+    src = gg.sample_sources(g, min(k, 13), seed=21)
+    src = np.tile(src, -(-k // src.size))[:k]
+    if g.n == 600 * 600:
+        src[0] = 0  # (counts past double's range)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        first = _auto(G, src)
+        _auto(G, gg.sample_sources(g, 40, seed=22))
+        G.single_source(180300 % g.n)  # (the lattice's middle: its counts fit double)
+        assert np.array_equal(first, _auto(G, src))
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        _auto(G, src[:1])
+        plain(G, src[1:2])
+        assert np.array_equal(first, _auto(G, src))
+
+
 def test_more_levels_than_the_first_estimate_and_trim():
     g = gg.path(21000)
     src = np.array([0, 20999, 10000, 3], np.int32)
