@@ -659,7 +659,18 @@ bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *
         range_exceeded(g);
     }
     const bool state = dist || sigma;  // per-source exports: not on the pair path
-    if (!state && use_pair(g, level_loop, width)) return pair_run(g, sources, k, bc_out, stream);
+    if (!state && use_pair(g, level_loop, width)) {
+        bc_status st = pair_run(g, sources, k, bc_out, stream);
+        if (st != BC_ERR_OUT_OF_MEMORY) return st;
+        // no room for the queues: what a graph that is not deep takes
+        (void)hipGetLastError();
+        (void)bc_trim_workspaces(g);
+        if (k < g->tuned_min_batched.load() && !g->sigma_ext.load()) {
+            st = plain_run(g, sources, k, bc_out, nullptr, stream, nullptr, nullptr);
+            if (st != BC_ERR_RANGE) return st;
+            range_exceeded(g);
+        }
+    }
     std::vector<int32_t> order, s_int;
     std::vector<BatchPlan> plan;
     {

@@ -135,8 +135,8 @@ static bc_status pair_room(bc_graph_s *g, PairWS *ws, int32_t k, const PairShape
 }
 
 // An idle workspace of the graph (calls return with their work finished), or
-// a new one, with room for k sources.
-static bc_status pair_acquire(bc_graph_s *g, int32_t k, const PairShape &sh, PairWS **out) {
+// a new one.
+static bc_status pair_acquire(bc_graph_s *g, PairWS **out) {
     PairWS *ws = nullptr;
     {
         std::lock_guard<std::mutex> lk(g->mu);
@@ -152,7 +152,7 @@ static bc_status pair_acquire(bc_graph_s *g, int32_t k, const PairShape &sh, Pai
         g->pair_pool.push_back(ws);
     }
     *out = ws;
-    return pair_room(g, ws, k, sh);
+    return BC_OK;
 }
 
 // The graph's pair-path vertex order, built on first use (kept with the graph).
@@ -279,16 +279,18 @@ static hipError_t solo_round(bc_graph_s *g, PairWS *ws, int32_t m, hipStream_t s
     return hipSuccess;
 }
 
-// All sources, as many at a time as the budget holds, each round's
-// dependencies added to bc_out (caller order) in source order.  Returns with
-// all work finished.
+// All sources, as many at a time as the budget and the free memory hold, each
+// round's dependencies added to bc_out (caller order) in source order.
+// Returns with all work finished; BC_ERR_OUT_OF_MEMORY where not even one
+// source at a time fits.
 bc_status pair_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_out,
                    hipStream_t stream) {
     const bc_status sl = pair_layout(g, stream);
     if (sl != BC_OK) return sl;
     PairShape sh = pair_shape(g, k);
+    int32_t most = std::max(k, 1);  // sources of a round that memory has room for
     PairWS *ws = nullptr;
-    bc_status st = pair_acquire(g, pair_cap(g, std::max(k, 1), sh), sh, &ws);
+    bc_status st = pair_acquire(g, &ws);
     struct Held {
         bc_graph_s *g;
         PairWS *&ws;
@@ -313,8 +315,14 @@ bc_status pair_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_
     int32_t run_depth = 0;
     int64_t level_steps = 0;
     for (int32_t s0 = 0; s0 < k;) {
-        const int32_t m = std::min(pair_cap(g, k, sh), k - s0);
+        const int32_t m = std::min({pair_cap(g, k, sh), most, k - s0});
         st = pair_room(g, ws, m, sh);
+        if (st == BC_ERR_OUT_OF_MEMORY && m > 1) {
+            (void)hipGetLastError();  // (or the next launch would report it)
+            most = m > kPairSum ? (m / 2 + kPairSum - 1) / kPairSum * kPairSum : m / 2;
+            most = std::min(most, m - 1);
+            continue;
+        }
         if (st != BC_OK) return st;
         PairDev &d = ws->dev;
         int32_t *h_src = ws->h_depth + m + 1;

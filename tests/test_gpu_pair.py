@@ -212,3 +212,56 @@ def test_rounds_of_sources():
     with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
         check_bc(batched(G, ten), oracle_bc(g, ten))
         check_bc(batched(G, src), want)
+
+
+class _LittleMemory:
+    """All of the device's memory but `leave` bytes taken (0: but for less than
+    16 MB, whatever the free size reported)."""
+
+    def __init__(self, leave):
+        self.leave = leave
+
+    def __enter__(self):
+        import torch
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        free, _ = torch.cuda.mem_get_info()
+        leave = self.leave or 64 << 20
+        self.blocks = [torch.empty(free - leave, dtype=torch.uint8, device="cuda")]
+        try:
+            while not self.leave and len(self.blocks) < 64:
+                self.blocks.append(torch.empty(16 << 20, dtype=torch.uint8, device="cuda"))
+        except torch.OutOfMemoryError:
+            pass
+
+    def __exit__(self, *exc):
+        import torch
+        self.blocks.clear()
+        torch.cuda.empty_cache()
+
+
+def test_fewer_sources_at_a_time_where_memory_is_short():
+    g = gg.grid_road(1000, 1000, seed=23)
+    some = gg.sample_sources(g, 10, seed=24)
+    src = np.tile(some, 15)  # 3 GB or more of scratch at once
+    want = 15.0 * oracle_bc(g, some)
+    import torch
+    out = torch.empty(g.n, dtype=torch.float64, device="cuda")
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        with _LittleMemory(1 << 30):
+            G.run_async(src, out)
+        check_bc(out.cpu().numpy(), want)
+        G.run_async(src, out)
+        check_bc(out.cpu().numpy(), want)
+
+
+def test_another_path_where_memory_has_no_room_for_the_queues():
+    g = gg.grid_road(1000, 1000, seed=23)
+    src = gg.sample_sources(g, 2, seed=25)
+    import torch
+    out = torch.empty(g.n, dtype=torch.float64, device="cuda")
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        plain(G, src)  # its workspace is pooled (and given back to the call below)
+        with _LittleMemory(0):
+            G.run_async(src, out)
+        check_bc(out.cpu().numpy(), oracle_bc(g, src))
