@@ -290,21 +290,26 @@ bc_status bc_run_detail(bc_graph_t g, const int32_t *sources, int32_t k, const b
 
 /* Device bytes one run with k sources and the given options would take for its
  * workspaces (for admission control): one per concurrent part, or the
- * device-resident loop's per-source scratch, at the graph's current level-array
- * estimate (a deeper graph grows it) and row width: while the graph's path
+ * device-resident loop's per-source scratch, or a deep graph's queues with its
+ * vertex order.  With BC_MODE_BATCHED and BC_LOOP_AUTO the largest of what bc_run_async,
+ * bc_run_detail, bc_run_multi and bc_run_graphs take for k sources (on a deep
+ * graph the last three take the host loop's workspaces).  At the graph's
+ * current level-array estimate (a deeper graph grows it; a pooled workspace that
+ * has grown counts as it is) and row width: while the graph's path
  * counts have fitted 32 bits, host-loop workspaces hold uint32 sigma rows, and
  * the run in which a count first passes 32 bits adds double rows (512 bytes
  * per vertex and 64 sources) to each part's workspace.  opt may be NULL. */
 bc_status bc_workspace_bytes(bc_graph_t g, int32_t k, const bc_options *opt, size_t *bytes);
 
 /* Free pooled workspaces that are idle (the idle entries of the one-source,
- * batched and device-resident loops' pools).
+ * batched and device-resident loops' pools and of the deep graphs' queues, and
+ * a deep graph's vertex order, which the next such run builds again).
  * Safe while other runs are in flight. */
 bc_status bc_trim_workspaces(bc_graph_t g);
 
 /* Device bytes the graph's BC workspace pools hold right now (idle or in use:
  * one-source and batched workspaces with their level arrays, the
- * device-resident loop's scratch), for admission control alongside
+ * device-resident loop's scratch, a deep graph's queues and vertex order), for admission control alongside
  * bc_workspace_bytes.  Excludes the graph itself (bc_graph_info), the SSSP and
  * PageRank workspaces, and a call's transient buffers. */
 bc_status bc_workspace_held(bc_graph_t g, size_t *bytes);

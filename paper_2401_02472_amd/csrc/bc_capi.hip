@@ -277,15 +277,28 @@ bc_status bc_workspace_bytes(bc_graph_t g, int32_t k, const bc_options *opt, siz
     const int32_t nb = (k + width - 1) / width;
     const int32_t H = width > kWave ? 2 : 1;
     const int32_t lcap = std::max(16, g->batch_depth_hint.load() + 8);
-    if (use_source(g, opt ? opt->level_loop : 0, k, width)) {
-        *bytes = source_bytes(g, k);
-    } else if (use_pair(g, opt ? opt->level_loop : 0, width)) {
-        *bytes = pair_bytes(g, k);
+    // the largest of what the calls with these sources may take: bc_run_async
+    // its own loop; the exports and bc_run_graphs the host loop on a deep
+    // graph; bc_run_multi a workgroup per source or the host loop in one part
+    const int32_t loop = opt ? opt->level_loop : 0;
+    auto host = [&](int32_t parts, int32_t halves) {
+        size_t one = batch_ws_bytes(g, halves) + batch_level_bytes(g, lcap, halves);
+        // (a pooled workspace whose level array or rows have grown further is reused)
+        std::lock_guard<std::mutex> lk(g->mu);
+        for (const BatchWS *ws : g->batch_pool)
+            if (ws->H == halves && ws->lcap)
+                one = std::max(one, ws->bytes + batch_level_bytes(g, ws->lcap, halves) + ws->src_cap);
+        return (size_t)parts * one;
+    };
+    size_t b = 0;
+    if (use_source(g, loop, k, width)) {
+        b = source_bytes(g, k);
     } else {
-        // one workspace per concurrent part
-        const int32_t parts = parts_of(g, opt ? opt->concurrency : 0, nb, H);
-        *bytes = (size_t)parts * (batch_ws_bytes(g, H) + batch_level_bytes(g, lcap, H));
+        b = host(parts_of(g, opt ? opt->concurrency : 0, nb, H), H);
+        if (use_pair(g, loop, width)) b = std::max(b, pair_bytes(g, k));
     }
+    if (loop == BC_LOOP_AUTO) b = std::max(b, multi_source(g) ? source_bytes(g, k) : host(1, 1));
+    *bytes = b;
     return BC_OK;
 }
 
@@ -314,6 +327,7 @@ bc_status bc_workspace_held(bc_graph_t g, size_t *bytes) {
         for (const SourceWS *ws : g->source_pool) b += ws->bytes;
         for (const PairWS *ws : g->pair_pool) b += ws->bytes;
     }
+    b += layout_held(g);
     *bytes = b;
     return BC_OK;
 }
@@ -344,6 +358,7 @@ bc_status bc_trim_workspaces(bc_graph_t g) {
     for (BatchWS *ws : idle_b) batch_ws_destroy(ws);
     for (SourceWS *ws : idle_s) source_ws_destroy(ws);
     for (PairWS *ws : idle_p) pair_ws_destroy(ws);
+    layout_trim(g);
     return BC_OK;
 }
 

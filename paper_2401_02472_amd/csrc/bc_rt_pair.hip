@@ -71,9 +71,33 @@ static int32_t pair_cap(const bc_graph_s *g, int32_t k, const PairShape &sh) {
     return (int32_t)std::max<int64_t>(1, std::min<int64_t>(k, std::max<int64_t>(fit, kPairSum)));
 }
 
+// Bytes of the vertex order: the rows pos, row_ptr and caller, the first arcs
+// and the ids; and of the scratch rows that building it takes besides.
+static size_t layout_row(const bc_graph_s *g) {
+    return align_up(((size_t)g->n + 1) * sizeof(int32_t));
+}
+static size_t layout_bytes(const bc_graph_s *g) {
+    return 3 * layout_row(g) + align_up((size_t)g->n * sizeof(int4)) +
+           align_up((size_t)std::max<int64_t>(g->nnz, 1) * sizeof(int32_t));
+}
+constexpr int kLayoutScratch = 6;
+
 size_t pair_bytes(const bc_graph_s *g, int32_t k) {
     const PairShape sh = pair_shape(g, std::max(k, 1));
-    return pair_ws_bytes(g, pair_cap(g, std::max(k, 1), sh), sh);
+    return layout_bytes(g) + std::max(pair_ws_bytes(g, pair_cap(g, std::max(k, 1), sh), sh),
+                                      kLayoutScratch * layout_row(g));
+}
+
+size_t layout_held(bc_graph_s *g) {
+    std::lock_guard<std::mutex> lk(g->layout_mu);
+    return g->layout.bytes;
+}
+
+void layout_trim(bc_graph_s *g) {
+    std::lock_guard<std::mutex> lk(g->layout_mu);
+    if (!g->layout.block || g->layout.users > 0) return;
+    (void)hipFree(g->layout.block);
+    g->layout = bc_graph_s::Layout{};
 }
 
 void pair_ws_destroy(PairWS *ws) {
@@ -89,11 +113,15 @@ void pair_ws_destroy(PairWS *ws) {
 static bc_status pair_room(bc_graph_s *g, PairWS *ws, int32_t k, const PairShape &sh) {
     const size_t need = pair_ws_bytes(g, k, sh);
     if (ws->bytes < need) {
+        auto set_bytes = [&](size_t b) {  // (bc_workspace_held reads it)
+            std::lock_guard<std::mutex> lk(g->mu);
+            ws->bytes = b;
+        };
         if (ws->block) (void)hipFree(ws->block);
         ws->block = nullptr;
-        ws->bytes = 0;
+        set_bytes(0);
         BC_TRY_HIP(hipMalloc(&ws->block, need));
-        ws->bytes = need;
+        set_bytes(need);
     }
     if (ws->depth_cap < k + 1) {
         if (ws->h_depth) (void)hipHostFree(ws->h_depth);
@@ -155,16 +183,20 @@ static bc_status pair_acquire(bc_graph_s *g, PairWS **out) {
     return BC_OK;
 }
 
-// The graph's pair-path vertex order, built on first use (kept with the graph).
-static bc_status pair_layout(bc_graph_s *g, hipStream_t stream) {
+// The graph's pair-path vertex order, built on first use, for one more run
+// (BC_OK: until layout_release).
+static bc_status layout_acquire(bc_graph_s *g, hipStream_t stream) {
     std::lock_guard<std::mutex> lk(g->layout_mu);
     auto &l = g->layout;
-    if (l.block) return BC_OK;
-    const size_t row = align_up(((size_t)g->n + 1) * sizeof(int32_t));
+    if (l.block) {
+        ++l.users;
+        return BC_OK;
+    }
+    const size_t row = layout_row(g);
     const size_t quad = align_up((size_t)g->n * sizeof(int4));
     void *block = nullptr, *tmp = nullptr;
-    hipError_t e = hipMalloc(&block, 3 * row + quad + align_up((size_t)std::max<int64_t>(g->nnz, 1) * sizeof(int32_t)));
-    if (e == hipSuccess) e = hipMalloc(&tmp, 6 * row);
+    hipError_t e = hipMalloc(&block, layout_bytes(g));
+    if (e == hipSuccess) e = hipMalloc(&tmp, kLayoutScratch * row);
     if (e == hipSuccess) {
         l.pos = (int32_t *)block;
         l.row_ptr = (int32_t *)((char *)block + row);
@@ -176,7 +208,7 @@ static bc_status pair_layout(bc_graph_s *g, hipStream_t stream) {
         d.row_ptr = g->d_row_ptr;
         d.col_idx = g->d_col_idx;
         d.iperm = g->d_iperm;
-        for (int i = 0; i < 6; ++i) d.tmp[i] = (int32_t *)((char *)tmp + (size_t)i * row);
+        for (int i = 0; i < kLayoutScratch; ++i) d.tmp[i] = (int32_t *)((char *)tmp + (size_t)i * row);
         d.pos = l.pos;
         d.new_rp = l.row_ptr;
         d.new_col = l.col_idx;
@@ -193,7 +225,14 @@ static bc_status pair_layout(bc_graph_s *g, hipStream_t stream) {
         return from_hip(e);
     }
     l.block = block;
+    l.bytes = layout_bytes(g);
+    l.users = 1;
     return BC_OK;
+}
+
+static void layout_release(bc_graph_s *g) {
+    std::lock_guard<std::mutex> lk(g->layout_mu);
+    --g->layout.users;
 }
 
 // How a round of sources ended: done, with a count past double's range, or
@@ -285,7 +324,7 @@ static hipError_t solo_round(bc_graph_s *g, PairWS *ws, int32_t m, hipStream_t s
 // source at a time fits.
 bc_status pair_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_out,
                    hipStream_t stream) {
-    const bc_status sl = pair_layout(g, stream);
+    const bc_status sl = layout_acquire(g, stream);
     if (sl != BC_OK) return sl;
     PairShape sh = pair_shape(g, k);
     int32_t most = std::max(k, 1);  // sources of a round that memory has room for
@@ -295,6 +334,7 @@ bc_status pair_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_
         bc_graph_s *g;
         PairWS *&ws;
         ~Held() {
+            layout_release(g);
             if (!ws) return;
             std::lock_guard<std::mutex> lk(g->mu);
             ws->busy = false;

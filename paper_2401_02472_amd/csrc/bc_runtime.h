@@ -302,10 +302,14 @@ struct bc_graph_s {
     bool deep = false;
     // pair-path runs keep exponents once a count passed double's range
     std::atomic<bool> pair_ext{false};
-    // the pair path's vertex order and the CSR in it (built on first use)
+    // the pair path's vertex order and the CSR in it (built on first use, a
+    // workspace like the pools': reported with them and trimmed while no run
+    // is using it)
     std::mutex layout_mu;
     struct Layout {
         void *block = nullptr;
+        size_t bytes = 0;
+        int32_t users = 0;
         int32_t *pos = nullptr, *row_ptr = nullptr, *col_idx = nullptr, *caller = nullptr;
         int4 *four = nullptr;
     } layout;
@@ -413,6 +417,8 @@ bool pair_fits(const bc_graph_s *g);
 bool use_pair(const bc_graph_s *g, int32_t level_loop, int32_t width);
 size_t pair_bytes(const bc_graph_s *g, int32_t k);
 void pair_ws_destroy(PairWS *ws);
+size_t layout_held(bc_graph_s *g);
+void layout_trim(bc_graph_s *g);
 bc_status pair_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *bc_out,
                    hipStream_t stream);
 

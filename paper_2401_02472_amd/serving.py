@@ -67,7 +67,8 @@ class GpuExecutor:
         """Workspace plus output bytes of one launch."""
         from . import BC_MODE_BATCHED, make_options
         G = self.graphs[graph_id]
-        # bc_run_multi runs its batches as one part (or in the device loop)
+        # bc_run_multi runs its batches as one part (or in the device loop);
+        # the figure covers it on deep graphs too, whose own calls take queues
         ws = G.workspace_bytes(max(k, 1), make_options(BC_MODE_BATCHED, concurrency=1))
         return int(ws) + self.output_bytes(graph_id, nreq)
 

@@ -265,3 +265,40 @@ def test_another_path_where_memory_has_no_room_for_the_queues():
         with _LittleMemory(0):
             G.run_async(src, out)
         check_bc(out.cpu().numpy(), oracle_bc(g, src))
+
+
+def _caterpillar():
+    """A deep tree of 23,230 vertices (one path between any two: counts of 1, so
+    the host loop keeps its narrow rows): 505 vertices in a row, three children
+    each, fourteen leaves to each of those."""
+    spine = np.arange(505)
+    kids = 505 + np.arange(3 * 505)
+    leaves = 4 * 505 + np.arange(42 * 505)
+    u = np.concatenate([spine[:-1], np.repeat(spine, 3), np.repeat(kids, 14)])
+    v = np.concatenate([spine[1:], kids, leaves])
+    return gg.csr_from_edges(46 * 505, u, v)
+
+
+def test_admission_covers_every_call_on_a_deep_graph():
+    """bc_workspace_bytes against the workspaces that the calls leave pooled: the
+    host loop's for requests (the call of the server), the queues and the vertex
+    order for a call of its own."""
+    import torch
+    g = _caterpillar()
+    src = np.array([0], np.int32)
+    want = oracle_bc(g, src)
+    opt = bcm.make_options(bcm.BC_MODE_BATCHED, concurrency=1)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        plain(G, src)
+        G.trim_workspaces()
+        out = torch.empty(g.n, dtype=torch.float64, device="cuda")
+        G.run_multi([src], [out])
+        check_bc(out.cpu().numpy(), want)
+        assert 0 < G.workspace_held() <= G.workspace_bytes(1, opt)
+        G.trim_workspaces()
+        check_bc(batched(G, src), want)
+        order = 28 * g.n + 4 * g.nnz
+        assert order < G.workspace_held() <= G.workspace_bytes(1, opt)
+        G.trim_workspaces()
+        assert G.workspace_held() == 0
+        check_bc(batched(G, src), want)  # the vertex order built again
