@@ -371,13 +371,13 @@ bc_status bc_profile_read(bc_graph_t g, bc_profile *out, int32_t reset);
 
 /*
  * Autotuner (the choices the library makes for BC_MODE_AUTO).  Times, on the
- * first min(k, 128) of `sources`, the sparse_div values at width 64 (on up to
- * 64 of them), then on the same batch the degree thresholds of the batched
- * path's work items (the cut above which a vertex is split into chunk items:
- * the graph's current one, then 4, 8, 16, 32, 64, 128; the chunk size: the
- * current one, then 64, 128, 256, 512, 1024 arcs), then widths 64, 32 and
- * 128 on the whole sample, and the
- * one-source-at-a-time path on up to 4 sources; stores the fastest batched
+ * host-driven loop, whose settings they are, and the first min(k, 128) of
+ * `sources`, the sparse_div values at width 64 (on up to 64 of them), then on
+ * the same batch the degree thresholds of the batched path's work items (the
+ * cut above which a vertex is split into chunk items: the graph's current one,
+ * then 4, 8, 16, 32, 64, 128; the chunk size: the current one, then 64, 128,
+ * 256, 512, 1024 arcs), then widths 64, 32 and 128 on the whole sample, and
+ * the one-source-at-a-time path on up to 4 sources; stores the fastest batched
  * settings in the graph, together with the source count from which
  * BC_MODE_AUTO takes the batched path (one batch's time over one plain
  * source's).  Later runs on g with BC_MODE_AUTO (and batch_width / sparse_div

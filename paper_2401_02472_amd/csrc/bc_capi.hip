@@ -35,10 +35,11 @@ int32_t batch_width_of(const bc_graph_s *g, const bc_options *opt, int32_t k) {
     if (opt && opt->batch_width > 0) return opt->batch_width;
     const int32_t w = g->tuned_width.load();
     // a tuned width above 64 was timed on a sample that ran on the host loop;
-    // where the whole run takes a workgroup per source, that is the faster
-    // choice
+    // where the whole run takes a workgroup per source or a deep graph's
+    // queues, that is the faster choice
     const int32_t loop = opt ? opt->level_loop : BC_LOOP_AUTO;
-    if (w > kWave && k > 0 && use_source(g, loop, k, kWave)) return kWave;
+    if (w > kWave && k > 0 && (use_source(g, loop, k, kWave) || use_pair(g, loop, kWave)))
+        return kWave;
     return w;
 }
 

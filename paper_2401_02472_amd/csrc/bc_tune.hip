@@ -218,9 +218,11 @@ bc_status bc_autotune(bc_graph_t g, const int32_t *sources, int32_t k, void *str
         }
         return BC_OK;
     };
+    // on the host-driven loop, whose settings these are (a small graph's workgroup
+    // per source and a deep graph's queues read none of them)
     auto batched = [&](int32_t count, int32_t width, int32_t div, double &ms) {
         return timed([&]() { return batched_run(g, sources, count, d_bc, width, div, 1,
-                                                BC_LOOP_AUTO, stream, nullptr, nullptr); }, ms);
+                                                BC_LOOP_HOST, stream, nullptr, nullptr); }, ms);
     };
     // sparse-step threshold at width 64 on one batch (the default first);
     // then the widths on the whole sample with the best threshold.  A setting

@@ -302,3 +302,27 @@ def test_admission_covers_every_call_on_a_deep_graph():
         G.trim_workspaces()
         assert G.workspace_held() == 0
         check_bc(batched(G, src), want)  # the vertex order built again
+
+
+@pytest.mark.parametrize("g", [gg.rmat(11, 9, seed=26), gg.grid_road(150, 147, seed=27)],
+                         ids=["small", "deep"])
+def test_autotune_times_the_loop_its_settings_belong_to(g):
+    """A small graph's own calls take a workgroup per source and a deep graph's
+    take queues, which read none of the tuned settings: the tuner times the host
+    loop there, and the calls stay as they were."""
+    src = gg.sample_sources(g, 100, seed=28)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        before = _auto(G, src)
+        G.profile_enable(True)
+        G.profile_read(reset=True)
+        assert not G.autotune(src)["cached"]
+        p = G.profile_read(reset=True)
+        assert p["fused"]["launches"] == 0 and p["forward"]["vertices"] > 0
+        assert np.array_equal(before, _auto(G, src))
+        p = G.profile_read(reset=True)
+        if g.n <= 20415:
+            assert p["fused"]["launches"] == 1
+        else:
+            assert p["forward"]["launches"] > 0 and p["forward"]["vertices"] == 0
+        G.profile_enable(False)
+        check_bc(before, oracle_bc(g, src))
