@@ -243,7 +243,8 @@ bc_status bc_run_multi(bc_graph_t g, const int32_t *sources, const int32_t *req_
  * launch for directed graphs), so many small graphs of uneven size share it;
  * the others run after it on the host-driven loop.  level_loop:
  * BC_LOOP_DEVICE, every graph small enough for that loop joins; BC_LOOP_HOST,
- * none does; BC_LOOP_AUTO, the graphs that would take it on their own join.
+ * none does; BC_LOOP_AUTO, the graphs for which that is estimated faster (where
+ * the two are near, it is for graphs that share the launch).
  * Each graph's result is bit-identical to bc_run_async on that graph with
  * BC_MODE_BATCHED, batch_width 64 and the loop reported in loops[i]; a graph
  * that needs the extended range runs on its own, as such a call would.

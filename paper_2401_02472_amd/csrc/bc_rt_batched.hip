@@ -531,9 +531,9 @@ bc_status run_batch_plan(bc_graph_s *g, const std::vector<int32_t> &s_int,
 bc_status run_graphs(bc_graph_s *const *gs, int32_t ng, const int32_t *const *sources,
                      const int32_t *ks, double *const *outs, int32_t level_loop,
                      int32_t *loops, hipStream_t stream) {
-    // the graphs whose own run would take a workgroup per source join
     std::vector<char> join((size_t)ng, 0);
-    for (int32_t i = 0; i < ng; ++i) join[(size_t)i] = use_source(gs[i], level_loop, ks[i], kWave);
+    for (int32_t i = 0; i < ng; ++i)
+        join[(size_t)i] = use_source(gs[i], level_loop, ks[i], kWave, ng > 1);
     std::vector<SourceJob> jobs;
     std::vector<int32_t> at, alone;
     for (int32_t i = 0; i < ng; ++i) {

@@ -314,42 +314,64 @@ bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
 }
 
 // Estimated times of a call's alternatives in seconds, fitted to measured
-// calls (MI355X, R-MAT of 1K to 16K vertices, uniform random, directed R-MAT):
-//   this path   k = 64: 0.069 ms at 21K arcs, 0.110 at 97K, 0.279 at 426K;
-//               k = 1024: 0.267 ms at 97K (two rounds of two per unit), 1.06
-//               at 426K; a single source alone at 426K arcs 0.475 (one unit
-//               waits for all its arcs to reach its L2)
-//   host loop   k = 64: 0.75, 0.67 and 0.79 ms; k = 1024: 4.1 and 5.6 ms
-//   one source  0.154, 0.166 and 0.185 ms, 0.10 .. 0.14 ms for each of many
-//   at a time
+// calls (MI355X, R-MAT of 4K to 16K vertices with edge factors 16 to 100,
+// uniform random of 1K to 20K with 4 to 900 arcs per vertex, directed R-MAT;
+// 16 to 4,096 sources).  For instance, ms of 64 sources on the host loop and
+// here: uniform random of 20K vertices with 50 arcs each 0.37 / 0.50, with 16
+// 0.75 / 0.35; R-MAT of 16K vertices with edge factor 64 0.62 / 0.62, with 16
+// 0.68 / 0.28.
+//   this path   rounds of as many sources as the device holds, by vertices and
+//               arcs (more where two workgroups share a compute unit, and where
+//               a directed graph's forward pass reads two rows; less where the
+//               ids are those of few vertices)
+//   host loop   0.045 ms per level of a batch, the levels by degree: the
+//               breadth of a uniform random graph with a tail where degrees are
+//               small, six more where they are skewed; batches run four at once
 static double source_seconds(const bc_graph_s *g, int32_t k) {
     const int32_t per = source_per_cu(g);
     const double rounds = std::ceil((double)k / ((double)kCus * per));
-    const double arc = k == 1 ? 1.0e-9 : (k > kCus && per > 1 ? 0.8e-9 : 0.6e-9);
-    return 25e-6 + rounds * (25e-6 + arc * (double)g->nnz);
+    const double arc = (g->directed ? 0.5e-9 : 0.35e-9) * std::min(1.0, (double)g->n / 8192.0);
+    const double work = 6e-9 * (double)g->n + arc * (double)g->nnz;
+    return 25e-6 + rounds * (25e-6 + work * (k > kCus && per > 1 ? 1.4 : 1.0));
 }
 static double host_seconds(const bc_graph_s *g, int32_t k) {
-    return 0.35e-3 + std::ceil((double)k / kWave) * (0.3e-3 + 0.15e-9 * (double)g->nnz);
-}
-static double plain_seconds(const bc_graph_s *g, int32_t k) {
-    return 50e-6 + (double)k * (0.105e-3 + 40e-12 * (double)g->nnz);
+    const double live = std::max(g->live_end, 2), arcs = (double)g->nnz;
+    const double degree = std::max(arcs / live, 1.5);
+    const bool skewed = g->arc_degree > 2.0 * degree;
+    const double levels = 1.3 + std::log(live) / std::log(degree) + 2.0 * std::log(live) / degree +
+                          (skewed ? 6.0 : 0.0);
+    const double batch = 0.045e-3 * levels + 0.115e-9 * arcs + 3e-9 * (double)g->n;
+    const double batches = std::ceil((double)k / kWave);
+    if (batches <= 1.0) return batch * (0.8 + 0.2 * (double)k / kWave);
+    return batch * (0.5 + (skewed ? 0.4 : 0.55) * batches);
 }
 
-// Whether a batched call of k sources takes this path.
-bool use_source(const bc_graph_s *g, int32_t level_loop, int32_t k, int32_t width) {
+// Few sources, where the one-source path is the alternative (R-MAT of 1K to
+// 16K vertices: 0.154, 0.166 and 0.185 ms for one, 0.10 .. 0.14 ms for each of
+// many; here 0.475 ms for one alone at 426K arcs, which waits for its arcs to
+// reach its L2, and 0.28 for several).  Beyond 1.3M arcs that path is faster
+// than this estimate of it (uniform random of 20K vertices with 100 arcs each,
+// 8 sources: 0.75 ms against 1.04).
+bool source_beats_plain(const bc_graph_s *g, int32_t k) {
+    const double arcs = (double)g->nnz;
+    const double here = 50e-6 + (k == 1 ? 1.0e-9 : 0.6e-9) * arcs;
+    return arcs < 1.3e6 && here < 50e-6 + (double)k * (0.105e-3 + 40e-12 * arcs);
+}
+
+// Whether a batched call of k sources takes this path.  `shared`: the call's other requests or graphs run beside these
+// sources here, but one after the other on the host loop.
+bool use_source(const bc_graph_s *g, int32_t level_loop, int32_t k, int32_t width, bool shared) {
     if (g->sigma_ext.load()) return false;  // extended range: host loop only
     if (width > kWave) return false;        // two lane words per vertex: host loop only
     if (!source_fits(g)) return false;
     if (level_loop == BC_LOOP_DEVICE) return true;
     if (level_loop == BC_LOOP_HOST || level_loop == BC_LOOP_GRAPH) return false;
-    return source_seconds(g, k) < host_seconds(g, k);
+    if (source_seconds(g, k) < (shared ? 1.8 : 1.0) * host_seconds(g, k)) return true;
+    // (for few sources the other choice is one at a time, not the host loop)
+    return !g->directed && k < g->tuned_min_batched.load() && source_beats_plain(g, k);
 }
 
-bool source_beats_plain(const bc_graph_s *g, int32_t k) {
-    return source_seconds(g, k) < plain_seconds(g, k);
-}
-
-bool multi_source(const bc_graph_s *g) { return use_source(g, BC_LOOP_AUTO, kWave, kWave); }
+bool multi_source(const bc_graph_s *g) { return use_source(g, BC_LOOP_AUTO, kWave, kWave, true); }
 
 // (a unit per source: what a call of many small requests takes)
 size_t source_bytes(const bc_graph_s *g, int32_t k) {

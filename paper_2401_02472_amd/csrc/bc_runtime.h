@@ -400,7 +400,8 @@ struct SourceJob {
     int32_t *dist = nullptr;
     double *sigma = nullptr;
 };
-bool use_source(const bc_graph_s *g, int32_t level_loop, int32_t k, int32_t width);
+bool use_source(const bc_graph_s *g, int32_t level_loop, int32_t k, int32_t width,
+                bool shared = false);
 bool source_beats_plain(const bc_graph_s *g, int32_t k);
 // Whether bc_run_multi's calls take it: by the graph alone, so that a
 // request's result does not depend on the requests it shares a call with.

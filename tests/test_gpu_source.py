@@ -121,3 +121,19 @@ def test_workspaces_are_reported_and_trimmed():
         G.trim_workspaces()
         assert G.workspace_held() == 0
         assert np.array_equal(want, _device(G, src))
+
+
+@pytest.mark.parametrize("g,k,device", [
+    (gg.erdos_renyi(10000, 100, seed=31), 40, False),   # few levels, many arcs
+    (gg.erdos_renyi(10000, 100, seed=31), 300, True),   # ... but five batches
+    (gg.rmat(12, 8, seed=32), 64, True),
+    (gg.erdos_renyi(MAX_N, 4, seed=33), 64, True),
+], ids=["dense", "dense-many", "rmat", "sparse"])
+def test_the_loop_that_a_call_takes(g, k, device):
+    src = gg.sample_sources(g, k, seed=34)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        G.profile_enable(True)
+        got = batched(G, src)
+        p = G.profile_read(reset=True)
+        assert (p["fused"]["launches"] > 0) == device
+        check_bc(got, oracle_bc(g, src))
