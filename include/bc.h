@@ -120,8 +120,9 @@ typedef struct bc_options {
  * grid-wide kernels and polls the depth.  DEVICE: one workgroup runs a whole
  * source (every level, with workgroup barriers, the source's values in LDS)
  * and all sources of the call go in one launch: for small graphs, where launch
- * and polling costs dominate.  A source's values must fit a compute unit's
- * LDS: graphs of more than 20,415 vertices take HOST.  AUTO picks the loop
+ * and polling costs dominate.  Graphs of more than 20,415 vertices, whose values
+ * do not fit a compute unit's LDS, keep them in memory, up to 131,072 vertices
+ * and where that is not estimated slower than HOST; the others take HOST.  AUTO picks the loop
  * with the lower estimated time for the call's source count; an undirected
  * graph of at most 16 arcs per vertex and 8 on average that is deep (more than
  * 48 levels from one of four vertices) takes per-source queues instead, a

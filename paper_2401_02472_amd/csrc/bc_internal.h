@@ -270,6 +270,7 @@ struct SourceUnit {
     double *row;       // [n]
     int32_t *q;        // [n]
     double *sig;       // [n]
+    double *val;       // [n + 1], where the values do not fit LDS
     uint32_t *lvl;     // [n + 2][kSrcClasses] level starts in the queues
     double *out;       // NULL, or the request's BC (caller order) written by this unit
     int32_t *dist;     // exports (caller order), NULL unless asked for:
@@ -286,11 +287,12 @@ struct SourceSum {
     double *out;
 };
 
-// LDS of a workgroup on a graph of n vertices.
+// Whether the values of a graph of n vertices fit LDS, and a workgroup's LDS.
+bool source_in_lds(int32_t n);
 size_t source_lds_bytes(int32_t n);
 // range[u.graph] is set to 1 where a count passes double's range.
 hipError_t source_run(const SourceUnit *units, int32_t nunits, const SourceGraph *graphs,
-                      const int32_t *sources, bool directed, size_t lds, int32_t *range,
+                      const int32_t *sources, bool directed, bool in_lds, size_t lds, int32_t *range,
                       unsigned long long *stats, hipStream_t stream);
 hipError_t source_sum(const SourceSum *sums, int32_t nsums, int32_t max_n, hipStream_t stream);
 

@@ -553,10 +553,12 @@ bc_status run_graphs(bc_graph_s *const *gs, int32_t ng, const int32_t *const *so
     }
     std::vector<char> over;
     const bc_status st = source_jobs(jobs, stream, over);
-    if (st != BC_OK) return st;
+    const bool no_room = st == BC_ERR_OUT_OF_MEMORY;  // the host loop may have some
+    if (no_room) (void)hipGetLastError();
+    else if (st != BC_OK) return st;
     for (size_t j = 0; j < at.size(); ++j) {
-        if (!over[j]) continue;
-        range_exceeded(gs[at[j]]);
+        if (!no_room && !over[j]) continue;
+        if (!no_room) range_exceeded(gs[at[j]]);
         alone.push_back(at[j]);
     }
     std::sort(alone.begin(), alone.end());
@@ -654,9 +656,11 @@ bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *
         }
         std::vector<char> over;
         const bc_status st = source_jobs(jobs, stream, over);
-        if (st != BC_OK || !over[0]) return st;
-        // a count beyond double's range sends the call to the host loop
-        range_exceeded(g);
+        // a count beyond double's range sends the call to the host loop, as
+        // does scratch that does not fit
+        if (st == BC_ERR_OUT_OF_MEMORY) (void)hipGetLastError();
+        else if (st != BC_OK || !over[0]) return st;
+        else range_exceeded(g);
     }
     const bool state = dist || sigma;  // per-source exports: not on the pair path
     if (!state && use_pair(g, level_loop, width)) {
@@ -762,8 +766,9 @@ bc_status multi_run(bc_graph_s *g, const int32_t *sources, const int32_t *req_st
             jobs[0].reqs.push_back({req_start[r], req_start[r + 1] - req_start[r], outs[r]});
         std::vector<char> over;
         const bc_status st = source_jobs(jobs, stream, over);
-        if (st != BC_OK || !over[0]) return st;
-        range_exceeded(g);  // the call runs again level-scaled
+        if (st == BC_ERR_OUT_OF_MEMORY) (void)hipGetLastError();
+        else if (st != BC_OK || !over[0]) return st;
+        else range_exceeded(g);  // the call runs again level-scaled
     }
     struct Share {
         int32_t req, first, lanes;  // sources [first, first + lanes) of the call

@@ -5,20 +5,28 @@
 
 namespace bcx {
 
-// A launch's scratch per graph is kept under this (room for every unit the
-// device runs at once: 0.7 MB each for the largest graph, 256 at a time);
-// longer calls take several launches.  A request's units (at most those) go in
-// one launch.
+// A launch's scratch per graph is kept under this, or under what every unit the
+// device runs at once takes (where values are in LDS 0.7 MB each for the largest
+// graph, 256 at a time; up to 4.7 MB where they are not); longer calls take
+// several launches.  A request's units (at most those) go in one launch.
 constexpr size_t kSourceBudget = (size_t)512 << 20;
 
-// A source's values fit LDS, and arc offsets in bytes fit 32 bits.
+// Largest graph that this path takes with the values in memory: beyond it the
+// host loop was faster on every measured shape (see source_seconds).
+constexpr int32_t kSrcMemN = 1 << 17;
+
+// A source's values fit LDS, or memory may hold them, and arc offsets in bytes
+// fit 32 bits.
 bool source_fits(const bc_graph_s *g) {
-    return source_lds_bytes(g->n) <= kSrcLdsBytes && g->nnz < ((int64_t)1 << 30);
+    return (source_in_lds(g->n) || g->n <= kSrcMemN) && g->nnz < ((int64_t)1 << 30);
 }
 
 // Workgroups of the graph a compute unit holds at once (by LDS; two of 16
-// waves are all its wave slots).
+// waves are all its wave slots).  With the values in memory one, where arcs are
+// many: two run each other's lines out of the L2 (16,384 sources, 21K vertices
+// of 16 arcs each: 92 ms with two, 73 with one; of 4 each 24 and 27).
 int32_t source_per_cu(const bc_graph_s *g) {
+    if (!source_in_lds(g->n) && g->nnz > 8 * (int64_t)g->n) return 1;
     return source_lds_bytes(g->n) * 2 <= kSrcLdsBytes ? 2 : 1;
 }
 
@@ -34,12 +42,14 @@ int32_t source_unit(const bc_graph_s *g, int32_t k) {
 size_t source_unit_bytes(const bc_graph_s *g) {
     const size_t n = (size_t)std::max<int32_t>(g->n, 1);
     return 2 * align_up(n * sizeof(double)) + align_up(n * sizeof(int32_t)) +
-           align_up((n + 2) * kSrcClasses * sizeof(uint32_t));
+           align_up((n + 2) * kSrcClasses * sizeof(uint32_t)) +
+           (source_in_lds(g->n) ? 0 : align_up((n + 1) * sizeof(double)));
 }
 
-// Units a launch runs of a call of `units`.
+// Units a launch runs of a call of `units` (a request's go in one launch).
 int32_t source_cap(const bc_graph_s *g, int64_t units) {
-    const int64_t fit = (int64_t)(kSourceBudget / source_unit_bytes(g));
+    const int64_t fit = std::max<int64_t>((int64_t)(kSourceBudget / source_unit_bytes(g)),
+                                          kCus * source_per_cu(g));
     return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::max<int64_t>(units, 1), fit));
 }
 
@@ -123,9 +133,9 @@ SourceGraph source_graph(const bc_graph_s *g) {
 }
 
 // Runs every job's requests: their units in as few launches as their scratch
-// allows (one each for the undirected and the directed
-// graphs of a round), then the rows of each request
-// added in unit order.  Returns with all work finished; over[i] is set for a
+// allows (one each for the undirected and the directed graphs of a round, with
+// the values in LDS and in memory), then the rows of each request added in unit
+// order.  Returns with all work finished; over[i] is set for a
 // job with a count past double's range (its outputs then mean nothing).
 bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
                       std::vector<char> &over) {
@@ -222,7 +232,7 @@ bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
         struct Launch {
             size_t first, count;
             size_t lds;
-        } launch[2];
+        } launch[4];
         std::vector<size_t> take(nj, 0);
         for (size_t j = 0; j < nj; ++j) {
             const SourceJob &job = jobs[j];
@@ -251,12 +261,12 @@ bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
             }
             more |= done_req[j] < job.reqs.size();
         }
-        for (int kind = 0; kind < 2; ++kind) {
+        for (int kind = 0; kind < 4; ++kind) {
             Launch &l = launch[kind];
             l = {nu, 0, 0};
             for (size_t j = 0; j < nj; ++j) {
                 const SourceJob &job = jobs[j];
-                if (kind != (job.g->directed ? 1 : 0)) continue;
+                if (kind != (job.g->directed ? 1 : 0) + (source_in_lds(job.g->n) ? 0 : 2)) continue;
                 if (take[j] == 0) continue;
                 const size_t n = (size_t)job.g->n;
                 const size_t per = source_unit_bytes(job.g);
@@ -278,6 +288,8 @@ bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
                     d.q = (int32_t *)cut(n * sizeof(int32_t));
                     d.lvl = (uint32_t *)cut((n + 2) * kSrcClasses * sizeof(uint32_t));
                     d.sig = (double *)cut(n * sizeof(double));
+                    d.val = source_in_lds(job.g->n) ? nullptr
+                                                    : (double *)cut((n + 1) * sizeof(double));
                     d.out = un.count == rq.k ? rq.out : nullptr;
                     d.dist = job.dist;
                     d.sigma = job.sigma;
@@ -287,13 +299,13 @@ bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
             }
             l.count = nu - l.first;
         }
-        for (int kind = 0; kind < 2 && e == hipSuccess; ++kind) {
+        for (int kind = 0; kind < 4 && e == hipSuccess; ++kind) {
             const Launch &l = launch[kind];
             if (l.count == 0) continue;
             e = timer.begin(BC_PROF_FUSED, stream);
             if (e == hipSuccess)
-                e = source_run(h_units + l.first, (int32_t)l.count, h_graphs, h_src, kind == 1,
-                               l.lds, h_range, d_stats, stream);
+                e = source_run(h_units + l.first, (int32_t)l.count, h_graphs, h_src, kind % 2 == 1,
+                               kind < 2, l.lds, h_range, d_stats, stream);
             if (e == hipSuccess) e = timer.end(stream);
         }
         if (e == hipSuccess) e = source_sum(h_sums, (int32_t)ns, max_n, stream);
@@ -314,36 +326,61 @@ bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
 }
 
 // Estimated times of a call's alternatives in seconds, fitted to measured
-// calls (MI355X, R-MAT of 4K to 16K vertices with edge factors 16 to 100,
-// uniform random of 1K to 20K with 4 to 900 arcs per vertex, directed R-MAT;
-// 16 to 4,096 sources).  For instance, ms of 64 sources on the host loop and
-// here: uniform random of 20K vertices with 50 arcs each 0.37 / 0.50, with 16
-// 0.75 / 0.35; R-MAT of 16K vertices with edge factor 64 0.62 / 0.62, with 16
-// 0.68 / 0.28.
-//   this path   rounds of as many sources as the device holds, by vertices and
-//               arcs (more where two workgroups share a compute unit, and where
-//               a directed graph's forward pass reads two rows; less where the
-//               ids are those of few vertices)
-//   host loop   0.045 ms per level of a batch, the levels by degree: the
-//               breadth of a uniform random graph with a tail where degrees are
-//               small, six more where they are skewed; batches run four at once
+// calls (MI355X, R-MAT of 4K to 131K vertices with edge factors 4 to 100,
+// uniform random of 1K to 100K with 4 to 900 arcs per vertex, directed R-MAT;
+// 1 to 16,384 sources).  For instance, ms on the host loop and here,
+//   values in LDS, 64 sources: uniform random of 20K vertices with 50 arcs each
+//     0.37 / 0.50, with 16 0.75 / 0.35; R-MAT of 16K vertices with edge factor
+//     64 0.62 / 0.62, with 16 0.68 / 0.28
+//   values in memory, 64 and 4,096 sources: uniform random of 21K vertices with
+//     4 arcs each 1.24 / 0.26 and 40 / 6.3; 50K with 4 1.34 / 0.64 and 43 / 22,
+//     with 16 1.06 / 1.85 and 39 / 76; 100K with 4 1.37 / 1.36 and 49 / 54;
+//     R-MAT of 33K vertices, edge factor 4 0.75 / 0.36 and 20.6 / 6.8, 65K
+//     0.85 / 0.75 and 22.0 / 17.9, 131K 0.94 / 1.80 and 27 / 48
+//
+// A graph whose arcs gather at few vertices, against one of even degrees.
+static bool skewed(const bc_graph_s *g) {
+    return g->arc_degree * (double)std::max(g->live_end, 1) > 2.0 * (double)g->nnz;
+}
+
+// This path: rounds of as many sources as the device holds, by vertices and arcs
+// (more where two workgroups share a compute unit, where a directed graph's
+// forward pass reads two rows, and where rows end just past a turn of 64 arcs;
+// less where the ids are those of few vertices).  With the values in memory a
+// time per source, and more as a round's 256 sources fill the L2s, a fifth of
+// that where hubs keep to few lines; with a margin, as its estimate varies more.
 static double source_seconds(const bc_graph_s *g, int32_t k) {
+    const double n = (double)g->n, arcs = (double)g->nnz;
+    const double degree = arcs / (double)std::max(g->live_end, 1);
+    if (!source_in_lds(g->n)) {
+        const double crowd = (skewed(g) ? 0.44e-9 : 2.2e-9) * (g->directed ? 1.7 : 1.0) *
+                             std::pow(n / 21000.0, 0.67) * arcs;
+        const double round = 4e-9 * n + 1.0e-9 * arcs + crowd * std::min(1.0, (double)k / kCus);
+        return (50e-6 + std::max(1.0, (double)k / kCus) * round) / 0.85;
+    }
     const int32_t per = source_per_cu(g);
     const double rounds = std::ceil((double)k / ((double)kCus * per));
-    const double arc = (g->directed ? 0.5e-9 : 0.35e-9) * std::min(1.0, (double)g->n / 8192.0);
-    const double work = 6e-9 * (double)g->n + arc * (double)g->nnz;
-    return 25e-6 + rounds * (25e-6 + work * (k > kCus && per > 1 ? 1.4 : 1.0));
+    double arc = (g->directed ? 0.45e-9 : 0.35e-9) * std::min(1.0, n / 8192.0);
+    if (!skewed(g) && degree > 64.0) arc *= std::ceil(degree / 64.0) * 64.0 / degree;
+    return 25e-6 + rounds * (25e-6 + (6e-9 * n + arc * arcs) * (k > kCus && per > 1 ? 1.4 : 1.0));
 }
+
+// Host loop: a time per level of a batch, more where degrees are even and small,
+// the levels by degree (the breadth of a uniform random graph, with a tail and
+// six more where degrees are skewed).  A batch of fewer sources takes less where levels are thin;
+// batches run four at once, sparse ones beside each other more easily.
 static double host_seconds(const bc_graph_s *g, int32_t k) {
-    const double live = std::max(g->live_end, 2), arcs = (double)g->nnz;
+    const double arcs = (double)g->nnz, live = std::max(g->live_end, 2);
     const double degree = std::max(arcs / live, 1.5);
-    const bool skewed = g->arc_degree > 2.0 * degree;
-    const double levels = 1.3 + std::log(live) / std::log(degree) + 2.0 * std::log(live) / degree +
-                          (skewed ? 6.0 : 0.0);
-    const double batch = 0.045e-3 * levels + 0.115e-9 * arcs + 3e-9 * (double)g->n;
+    const double breadth = 1.3 + std::log(live) / std::log(degree);
+    const bool skew = skewed(g), thin = !skew && degree < 32.0;
+    const double few = std::min(1.0, 256.0 / (degree * degree));
+    const double levels = skew ? 0.045e-3 * (breadth + 2.0 * std::log(live) / degree + 6.0)
+                               : (0.05e-3 + 0.078e-3 * few) * breadth;
+    const double batch = levels + 0.115e-9 * arcs + 3e-9 * (double)g->n;
     const double batches = std::ceil((double)k / kWave);
-    if (batches <= 1.0) return batch * (0.8 + 0.2 * (double)k / kWave);
-    return batch * (0.5 + (skewed ? 0.4 : 0.55) * batches);
+    if (batches <= 1.0) return batch * std::pow((double)k / kWave, thin ? 0.25 : 0.1);
+    return batch * (skew ? 0.5 + 0.4 * batches : (thin ? 0.5 + 0.5 * batches : 0.4 + 0.65 * batches));
 }
 
 // Few sources, where the one-source path is the alternative (R-MAT of 1K to
@@ -354,24 +391,37 @@ static double host_seconds(const bc_graph_s *g, int32_t k) {
 // 8 sources: 0.75 ms against 1.04).
 bool source_beats_plain(const bc_graph_s *g, int32_t k) {
     const double arcs = (double)g->nnz;
-    const double here = 50e-6 + (k == 1 ? 1.0e-9 : 0.6e-9) * arcs;
+    const double here = source_in_lds(g->n) ? 50e-6 + (k == 1 ? 1.0e-9 : 0.6e-9) * arcs
+                                            : source_seconds(g, k);
     return arcs < 1.3e6 && here < 50e-6 + (double)k * (0.105e-3 + 40e-12 * arcs);
 }
 
-// Whether a batched call of k sources takes this path.  `shared`: the call's other requests or graphs run beside these
-// sources here, but one after the other on the host loop.
+// Whether a batched call of k sources takes this path.  `shared`: the call's
+// other graphs run beside these sources here, but one after the other on the
+// host loop.
 bool use_source(const bc_graph_s *g, int32_t level_loop, int32_t k, int32_t width, bool shared) {
     if (g->sigma_ext.load()) return false;  // extended range: host loop only
     if (width > kWave) return false;        // two lane words per vertex: host loop only
     if (!source_fits(g)) return false;
-    if (level_loop == BC_LOOP_DEVICE) return true;
     if (level_loop == BC_LOOP_HOST || level_loop == BC_LOOP_GRAPH) return false;
-    if (source_seconds(g, k) < (shared ? 1.8 : 1.0) * host_seconds(g, k)) return true;
+    const bool lds = source_in_lds(g->n);
+    if (level_loop == BC_LOOP_DEVICE && lds) return true;
+    if (level_loop == BC_LOOP_AUTO && !shared && !lds && g->deep) return false;  // as queues
+    // (a graph that joins others in a call runs here alone under DEVICE, too)
+    const bool lean = shared || level_loop == BC_LOOP_DEVICE;
+    if (source_seconds(g, k) < (lean ? (lds ? 1.8 : 1.3) : 1.0) * host_seconds(g, k)) return true;
     // (for few sources the other choice is one at a time, not the host loop)
     return !g->directed && k < g->tuned_min_batched.load() && source_beats_plain(g, k);
 }
 
-bool multi_source(const bc_graph_s *g) { return use_source(g, BC_LOOP_AUTO, kWave, kWave, true); }
+// By the 64-source call, and with the values in memory by the one-source call
+// too, which loses more there than it would with them in LDS.
+bool multi_source(const bc_graph_s *g) {
+    if (source_in_lds(g->n)) return use_source(g, BC_LOOP_AUTO, kWave, kWave, true);
+    return use_source(g, BC_LOOP_DEVICE, kWave, kWave) &&
+           source_seconds(g, kWave) < host_seconds(g, kWave) &&
+           source_seconds(g, 1) < 1.3 * host_seconds(g, 1);
+}
 
 // (a unit per source: what a call of many small requests takes)
 size_t source_bytes(const bc_graph_s *g, int32_t k) {

@@ -24,6 +24,8 @@
 //          of more than 512 arcs take a wave each, of 65 .. 512 arcs 16
 //          lanes, of 9 .. 64 arcs 4 lanes, of up to 8 arcs one lane.
 //   sig    sigma in queue order (global), for the reverse pass.
+// Larger graphs (kMem) keep val in memory, where 0 takes the place of both
+// sentinels, and in LDS a bit per vertex for the claims and one for the queued.
 // A vertex's sums run over its arcs in a fixed order (each lane its arcs in
 // turn, then a butterfly), whatever order the queue has, so results repeat
 // bit for bit.
@@ -37,7 +39,12 @@
 // 64 sources (64-value rows in global memory): all sources of the 4K-vertex
 // R-MAT (edge factor 8) 4.48 -> 0.71 ms, 16 graphs of 1K to 4K vertices with
 // 64 sources each in one call 5.75 -> 0.26 ms; against the one-source path,
-// one source of the 4K-vertex R-MAT 0.173 -> 0.084 ms.
+// one source of the 4K-vertex R-MAT 0.173 -> 0.084 ms.  With the values in
+// memory it is bound by their lines in the L2 (a compute unit's 8 n bytes, 32
+// units to a 4 MB L2): 16,384 sources on 21K vertices of 4 arcs each take 24.4
+// ms, the host loop 160; of the 33K-vertex R-MAT (edge factor 4) 26.8 and 80.4;
+// 32 graphs of 30K vertices, 64 sources each in one call, 6.6 and 42.9.  (One
+// workgroup per 64-source batch, as these graphs once ran: 52, 52.5 and 32.8.)
 #include "bc_internal.h"
 #include "bc_wave.h"
 
@@ -97,7 +104,8 @@ struct SrcView {
     int32_t n;
     int32_t c1, c2, c3;   // class c's ids and queue start at 0, c1, c2, c3
     const int32_t *row_ptr, *col_idx, *row_ptr_in, *col_idx_in;
-    double *val;          // LDS [n + 1], entry n always 0
+    double *val;          // [n + 1], entry n always 0; in LDS but with kMem
+    uint32_t *seen, *done;  // kMem: bits in LDS of the vertices claimed, of those queued
     int32_t *q;           // [n]: the classes' queues
     double *sig;          // [n]: sigma, in queue order
     __device__ __forceinline__ int32_t base(int c) const {
@@ -108,16 +116,55 @@ struct SrcView {
     }
 };
 
+// A vertex's value: with kMem the sentinel for one not claimed in the forward
+// pass (kFwd), whose memory holds 0.
+template <bool kMem, bool kFwd>
+__device__ __forceinline__ double value_of(const SrcView &s, int32_t id) {
+    if (kMem && kFwd && !((s.seen[id >> 5] >> (id & 31)) & 1u))
+        return __hiloint2double((int)kUnreachedHi, 0);
+    return s.val[id];
+}
+
 // Builds the queues of level L+1 from the vertices that level L claimed, the
 // ones whose value is 0: 64 ids per wave and turn, their places in the queues
 // taken with one LDS atomic per class among them.  `start`: the level's queue
 // positions, cnt_next: its counts so far.  The scan of n LDS words costs less
 // than a queue append per claim: a claim is then a plain store, and the queue
 // comes out in id order, neighbouring rows beside each other.
+template <bool kMem>
 __device__ __forceinline__ void collect(const SrcView &s, uint32_t *cnt_next,
                                         const uint32_t (&start)[kSrcClasses]) {
     BC_FULL_EXEC();
     const int lane = lane_id();
+    if constexpr (kMem) {  // the claims are 32 to a word, a word per lane
+        const int32_t words = (s.n + 32) / 32;
+        for (int32_t w0 = (int32_t)(threadIdx.x & ~(kWave - 1u)); w0 < words; w0 += kSrcBlock) {
+            const int32_t w = w0 + lane;
+            uint32_t got = 0;
+            if (w < words) {
+                const uint32_t now = s.seen[w];
+                got = now & ~s.done[w];
+                s.done[w] = now;
+            }
+            if (__ballot(got != 0u) == 0ull) continue;
+#pragma unroll
+            for (int c = 0; c < kSrcClasses; ++c) {
+                if (s.past(c) <= 32 * w0 || s.base(c) >= 32 * (w0 + kWave)) continue;
+                const int32_t b = s.base(c) - 32 * w, e = s.past(c) - 32 * w;
+                uint32_t m = got;  // ... those of the class: bits [b, e)
+                if (b > 0) m = b < 32 ? m & (~0u << b) : 0u;
+                if (e < 32) m = e > 0 ? m & ~(~0u << e) : 0u;
+                if (__ballot(m != 0u) == 0ull) continue;
+                uint32_t total;
+                const uint32_t mine = wave_excl_scan((uint32_t)__popc(m), total);
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&cnt_next[c], total);
+                at = (uint32_t)uniform((int32_t)at) + (uint32_t)s.base(c) + start[c] + mine;
+                for (; m; m &= m - 1u) s.q[at++] = 32 * w + __builtin_ctz(m);
+            }
+        }
+        return;
+    }
     for (int32_t v0 = (int32_t)(threadIdx.x & ~(kWave - 1u)); v0 < s.n; v0 += kSrcBlock) {
         const int32_t v = v0 + lane;
         const bool got = v < s.n && __double2hiint(s.val[v]) == 0;
@@ -171,7 +218,7 @@ __device__ __forceinline__ Ids ids_at(const int32_t *col, Row r) {
 // Calls body(ids, values) for every four arcs of each lane's row, the next
 // four ids already on their way (W lanes per vertex; slots past the row's end
 // get id n, whose value is 0).
-template <int W, typename Body>
+template <int W, bool kMem, bool kFwd, typename Body>
 __device__ __forceinline__ void over_row(const SrcView &s, const int32_t *col, Row r,
                                          Body &&body) {
     Ids nx = ids_at(col, r);
@@ -185,7 +232,7 @@ __device__ __forceinline__ void over_row(const SrcView &s, const int32_t *col, R
 #pragma unroll
         for (int u = 0; u < 4; ++u) x.id[u] = u < left ? x.id[u] : s.n;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) y[u] = s.val[x.id[u]];
+        for (int u = 0; u < 4; ++u) y[u] = value_of<kMem, kFwd>(s, x.id[u]);
         body(x, y);
     }
 }
@@ -215,35 +262,38 @@ __device__ __forceinline__ void pull4(const SrcView &s, const Ids &x, const doub
 }
 
 // Claims the unreached ones of four neighbours for level L+1 (NaN -> 0 by its
-// high word; every claimer stores the same).
+// high word; every claimer stores the same; with kMem, their bits).
+template <bool kMem>
 __device__ __forceinline__ void push4(const SrcView &s, const Ids &x, const double (&y)[4]) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-        if ((uint32_t)__double2hiint(y[u]) == kUnreachedHi)
-            *(reinterpret_cast<volatile uint32_t *>(&s.val[x.id[u]]) + 1) = 0u;
+        if ((uint32_t)__double2hiint(y[u]) == kUnreachedHi) {
+            if (kMem) atomicOr(&s.seen[x.id[u] >> 5], 1u << (x.id[u] & 31));
+            else *(reinterpret_cast<volatile uint32_t *>(&s.val[x.id[u]]) + 1) = 0u;
+        }
 }
 
 // Forward step of one vertex per W lanes: sigma over the arcs into it from
 // level L-1 (sign `par`), unreached neighbours claimed for level L+1.
 // Undirected graphs read each adjacency row once for both.
-template <int W, bool kDir, bool kStat>
+template <int W, bool kDir, bool kMem, bool kStat>
 __device__ __forceinline__ void fwd_vertex(const SrcView &s, const Task &k, bool source,
                                            double par, int32_t *range, SrcWork &wk) {
     double acc = 0.0;
     if (kDir) {
-        over_row<W>(s, s.col_idx_in, k.in,
+        over_row<W, kMem, true>(s, s.col_idx_in, k.in,
                     [&](const Ids &x, const double (&y)[4]) __attribute__((always_inline)) {
                         pull4<kStat>(s, x, y, par, acc, wk);
                     });
-        over_row<W>(s, s.col_idx, k.out,
+        over_row<W, kMem, true>(s, s.col_idx, k.out,
                     [&](const Ids &x, const double (&y)[4]) __attribute__((always_inline)) {
-                        push4(s, x, y);
+                        push4<kMem>(s, x, y);
                     });
     } else {
-        over_row<W>(s, s.col_idx, k.out,
+        over_row<W, kMem, true>(s, s.col_idx, k.out,
                     [&](const Ids &x, const double (&y)[4]) __attribute__((always_inline)) {
                         pull4<kStat>(s, x, y, par, acc, wk);
-                        push4(s, x, y);
+                        push4<kMem>(s, x, y);
                     });
     }
     acc = lanes_sum<W>(acc);
@@ -259,11 +309,11 @@ __device__ __forceinline__ void fwd_vertex(const SrcView &s, const Task &k, bool
 // Reverse step of one vertex per W lanes: the children's c summed (sign
 // `child`; no arcs are passed at the deepest level), delta = sigma * sum
 // added to the unit's BC row.
-template <int W, bool kStat>
+template <int W, bool kMem, bool kStat>
 __device__ __forceinline__ void bwd_vertex(const SrcView &s, const Task &k, double child,
                                            double *row, bool first, SrcWork &wk) {
     double acc = 0.0;
-    over_row<W>(s, s.col_idx, k.out,
+    over_row<W, kMem, false>(s, s.col_idx, k.out,
                 [&](const Ids &x, const double (&y)[4]) __attribute__((always_inline)) {
                     pull4<kStat>(s, x, y, child, acc, wk);
                 });
@@ -336,7 +386,7 @@ __device__ __forceinline__ void over_level(const SrcView &s, const uint32_t (&lo
 
 // One workgroup per unit: the unit's sources one after another, their
 // dependencies added to the unit's BC row in that order.
-template <bool kDir, bool kStat>
+template <bool kDir, bool kMem, bool kStat>
 __global__ __launch_bounds__(kSrcBlock, 8) void
 k_source(const SourceUnit *units, const SourceGraph *graphs, const int32_t *sources,
          int32_t *range_flags, unsigned long long *stats) {
@@ -355,7 +405,11 @@ k_source(const SourceUnit *units, const SourceGraph *graphs, const int32_t *sour
     s.col_idx = uniform(graphs[gi].col_idx);
     s.row_ptr_in = uniform(graphs[gi].row_ptr_in);
     s.col_idx_in = uniform(graphs[gi].col_idx_in);
-    s.val = lds;
+    const int32_t words = (n + 32) / 32;  // bits of the vertices and of entry n
+    s.seen = reinterpret_cast<uint32_t *>(lds);
+    s.done = s.seen + words;
+    if constexpr (kMem) s.val = uniform(un.val);
+    else s.val = lds;
     s.q = uniform(un.q);
     s.sig = uniform(un.sig);
     double *row = uniform(un.row);
@@ -371,9 +425,16 @@ k_source(const SourceUnit *units, const SourceGraph *graphs, const int32_t *sour
     for (int32_t v = t; v < n; v += kSrcBlock) row[v] = 0.0;
     for (int32_t i = 0; i < count; ++i) {
         const int32_t src = uniform(sources[first + i]);
-        const double unreached = __hiloint2double((int)kUnreachedHi, 0);
+        const double unreached = kMem ? 0.0 : __hiloint2double((int)kUnreachedHi, 0);
         for (int32_t v = t; v <= n; v += kSrcBlock)
             s.val[v] = v == src || v == n ? 0.0 : unreached;
+        if (kMem)
+            for (int32_t w = t; w < words; w += kSrcBlock) {
+                const uint32_t x = (w == src >> 5 ? 1u << (src & 31) : 0u) |
+                                   (w == n >> 5 ? 1u << (n & 31) : 0u);
+                s.seen[w] = x;
+                s.done[w] = x;
+            }
         if (t < 3 * kSrcClasses) (&cnt[0][0])[t] = 0;
         int sc = 0;
         int32_t q0 = 0;
@@ -405,13 +466,13 @@ k_source(const SourceUnit *units, const SourceGraph *graphs, const int32_t *sour
             const double par = (L & 1) ? 1.0 : -1.0;  // sign of level L-1
             over_level<true, kDir, false>(s, lo, hi, [&](int cls, const Task &k)
                                           __attribute__((always_inline)) {
-                if (cls == 0) fwd_vertex<kWave, kDir, kStat>(s, k, L == 0, par, range, wf);
-                else if (cls == 1) fwd_vertex<16, kDir, kStat>(s, k, L == 0, par, range, wf);
-                else if (cls == 2) fwd_vertex<4, kDir, kStat>(s, k, L == 0, par, range, wf);
-                else fwd_vertex<1, kDir, kStat>(s, k, L == 0, par, range, wf);
+                if (cls == 0) fwd_vertex<kWave, kDir, kMem, kStat>(s, k, L == 0, par, range, wf);
+                else if (cls == 1) fwd_vertex<16, kDir, kMem, kStat>(s, k, L == 0, par, range, wf);
+                else if (cls == 2) fwd_vertex<4, kDir, kMem, kStat>(s, k, L == 0, par, range, wf);
+                else fwd_vertex<1, kDir, kMem, kStat>(s, k, L == 0, par, range, wf);
             });
             __syncthreads();
-            collect(s, cn, hi);
+            collect<kMem>(s, cn, hi);
             __syncthreads();
             uint32_t found = 0;
 #pragma unroll
@@ -456,10 +517,10 @@ k_source(const SourceUnit *units, const SourceGraph *graphs, const int32_t *sour
             for (int c = 0; c < kSrcClasses; ++c) prev[c] = lvl[(size_t)(x - 1) * kSrcClasses + c];
             const double child = (x & 1) ? 1.0 : -1.0;  // sign of level x+1
             auto settle = [&](int cls, const Task &k) __attribute__((always_inline)) {
-                if (cls == 0) bwd_vertex<kWave, kStat>(s, k, child, row, i == 0, wb);
-                else if (cls == 1) bwd_vertex<16, kStat>(s, k, child, row, i == 0, wb);
-                else if (cls == 2) bwd_vertex<4, kStat>(s, k, child, row, i == 0, wb);
-                else bwd_vertex<1, kStat>(s, k, child, row, i == 0, wb);
+                if (cls == 0) bwd_vertex<kWave, kMem, kStat>(s, k, child, row, i == 0, wb);
+                else if (cls == 1) bwd_vertex<16, kMem, kStat>(s, k, child, row, i == 0, wb);
+                else if (cls == 2) bwd_vertex<4, kMem, kStat>(s, k, child, row, i == 0, wb);
+                else bwd_vertex<1, kMem, kStat>(s, k, child, row, i == 0, wb);
             };
             if (x == deepest) over_level<false, false, true>(s, lo, end, settle);
             else over_level<true, false, true>(s, lo, end, settle);
@@ -525,14 +586,21 @@ __global__ __launch_bounds__(kBlock) void k_source_sum(const SourceSum *sums) {
 unsigned int exec_partial_source() { return exec_partial_take(); }
 #endif
 
-size_t source_lds_bytes(int32_t n) { return ((size_t)n + 1) * sizeof(double); }
+bool source_in_lds(int32_t n) { return ((size_t)n + 1) * sizeof(double) <= kSrcLdsBytes; }
+
+size_t source_lds_bytes(int32_t n) {
+    if (source_in_lds(n)) return ((size_t)n + 1) * sizeof(double);
+    return 2 * (((size_t)n + 32) / 32) * sizeof(uint32_t);
+}
 
 hipError_t source_run(const SourceUnit *units, int32_t nunits, const SourceGraph *graphs,
-                      const int32_t *sources, bool directed, size_t lds, int32_t *range,
+                      const int32_t *sources, bool directed, bool in_lds, size_t lds, int32_t *range,
                       unsigned long long *stats, hipStream_t stream) {
     if (nunits <= 0) return hipSuccess;
-    auto k = directed ? (stats ? k_source<true, true> : k_source<true, false>)
-                      : (stats ? k_source<false, true> : k_source<false, false>);
+    auto k = in_lds ? (directed ? (stats ? k_source<true, false, true> : k_source<true, false, false>)
+                                : (stats ? k_source<false, false, true> : k_source<false, false, false>))
+                    : (directed ? (stats ? k_source<true, true, true> : k_source<true, true, false>)
+                                : (stats ? k_source<false, true, true> : k_source<false, true, false>));
     hipLaunchKernelGGL(k, dim3(nunits), dim3(kSrcBlock), lds, stream, units, graphs, sources,
                        range, stats);
     return hipGetLastError();

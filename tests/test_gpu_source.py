@@ -9,7 +9,8 @@ import pytest
 import graphgen as gg
 import oracle
 import paper_2401_02472_amd as bcm
-from tests.gpu_checks import batched, check_bc, check_sigma, oracle_bc
+from tests.gpu_checks import batched, check_bc, check_sigma, oracle_bc, run_mode
+from tests.test_gpu_pair import _LittleMemory
 
 pytestmark = pytest.mark.gpu
 
@@ -137,3 +138,112 @@ def test_the_loop_that_a_call_takes(g, k, device):
         p = G.profile_read(reset=True)
         assert (p["fused"]["launches"] > 0) == device
         check_bc(got, oracle_bc(g, src))
+
+
+def _back_arcs(n):
+    """A directed graph of n vertices: a path of 70 levels whose vertices also
+    point back, a dense part, and a sparse rest."""
+    pairs = [(i, i + 1) for i in range(69)]
+    pairs += [(i, j) for i in range(70) for j in range(i) if (i * 7 + j) % 3 == 0]
+    rng = np.random.default_rng(n)
+    pairs += [(int(a), int(b)) for a, b in rng.integers(0, 400, (3000, 2)) if a != b]
+    pairs += [(int(a), int(b)) for a, b in rng.integers(0, n, (2 * n, 2)) if a != b]
+    return gg.directed(n, pairs, "back-arcs")
+
+
+@pytest.mark.parametrize("g,k", [
+    (gg.erdos_renyi(MAX_N + 1, 4, seed=35), 70),          # the first past the LDS
+    (gg.erdos_renyi(20448, 3, seed=36), 600),             # 639 whole words of bits
+    (gg.erdos_renyi(20447, 3, seed=36), 600), (gg.erdos_renyi(20449, 3, seed=36), 1),
+    (_hubs([7, 8, 9, 10, 63, 64, 65, 66, 511, 512, 513, 514, 1025, 3, 4, 5] + [3] * 9000, 22000), 40),
+    (gg.rmat(15, 5, seed=37), 300),
+    (gg.erdos_renyi(131072, 2, seed=38), 20),             # the largest ...
+    (_back_arcs(30011), 90), (_back_arcs(20416), 600),
+], ids=["first", "words", "words-1", "words+1", "hubs", "rmat", "largest", "back", "back-many"])
+def test_values_in_memory(g, k):
+    """Graphs whose values do not fit LDS: a bit per vertex there instead."""
+    directed = g.name == "back-arcs"
+    src = gg.sample_sources(g, min(k, 50), seed=39)
+    src = np.tile(src, -(-k // src.size))[:k]
+    want, st = oracle.bc(g.row_ptr, g.col_idx, src, directed=directed)
+    assert st == oracle.OK
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx, bcm.BC_GRAPH_DIRECTED if directed else 0) as G:
+        got = _device(G, src)
+        check_bc(got, want)
+        assert np.array_equal(got, _device(G, src))
+        opt = bcm.make_options(bcm.BC_MODE_BATCHED, level_loop=bcm.BC_LOOP_DEVICE)
+        few = src[:3]
+        _, dist, sigma = G.run_detail(few, opt)
+        for i in range(few.size):
+            od, osg, _, _ = oracle.single_source(g.row_ptr, g.col_idx, int(few[i]),
+                                                 with_delta=False, directed=directed)
+            assert np.array_equal(dist[i], od)
+            check_sigma(sigma[i], osg)
+        G.profile_enable(True)
+        G.profile_read(reset=True)
+        assert np.array_equal(got, _device(G, src))
+        p = G.profile_read(reset=True)
+        assert p["fused"]["launches"] == 1, "not the device-resident loop"
+        G.profile_enable(False)
+        assert 0 < G.workspace_held() <= G.workspace_bytes(k, opt)
+
+
+def test_graph_beyond_the_values_in_memory():
+    g = gg.erdos_renyi(131073, 2, seed=38)
+    src = gg.sample_sources(g, 20, seed=39)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        G.profile_enable(True)
+        check_bc(_device(G, src), oracle_bc(g, src))
+        assert G.profile_read(reset=True)["fused"]["launches"] == 0
+
+
+def test_thousands_of_sources_past_the_lds_limit():
+    """Exact-BC-like calls: one launch of a workgroup per source, not batches."""
+    g = gg.erdos_renyi(21000, 4, seed=40)
+    some = gg.sample_sources(g, 64, seed=41)
+    src = np.tile(some, 16)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        G.profile_enable(True)
+        got = run_mode(G, src, bcm.BC_MODE_AUTO)
+        assert G.profile_read(reset=True)["fused"]["launches"] == 1
+        check_bc(got, 16.0 * oracle_bc(g, some))
+
+
+def test_requests_and_graphs_past_the_lds_limit():
+    """Requests equal the ones alone and graphs that join a call their own runs,
+    with the values in LDS and in memory, undirected and directed."""
+    import torch
+    g = gg.erdos_renyi(25001, 4, seed=42)
+    reqs = [gg.sample_sources(g, k, seed=43 + k) for k in (1, 8, 64, 5, 300, 1)]
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        outs = [torch.full((g.n,), -1.0, dtype=torch.float64, device="cuda") for _ in reqs]
+        G.run_multi(reqs, outs)
+        for r, o in zip(reqs, outs):
+            alone = torch.full((g.n,), -1.0, dtype=torch.float64, device="cuda")
+            G.run_multi([r], [alone])
+            assert torch.equal(o, alone)
+            check_bc(o.cpu().numpy(), oracle_bc(g, r))
+    gs = [gg.rmat(11, 8, seed=44), g, _back_arcs(22222), gg.directed(50, [(i, i + 1) for i in range(49)], "p"),
+          gg.erdos_renyi(60000, 3, seed=45)]
+    dirs = [False, False, True, True, False]
+    Gs = [bcm.Graph(x.n, x.row_ptr, x.col_idx, bcm.BC_GRAPH_DIRECTED if d else 0)
+          for x, d in zip(gs, dirs)]
+    srcs = [gg.sample_sources(x, min(40, x.n - 1), seed=46) for x in gs]
+    outs = [torch.full((x.n,), -1.0, dtype=torch.float64, device="cuda") for x in gs]
+    loops = bcm.bc_run_graphs(Gs, srcs, outs)
+    assert all(lp == bcm.BC_LOOP_DEVICE for lp in loops)
+    for x, d, G, s, o, lp in zip(gs, dirs, Gs, srcs, outs, loops):
+        own = batched(G, s, level_loop=lp, batch_width=64)
+        assert np.array_equal(o.cpu().numpy(), own)
+        check_bc(own, oracle.bc(x.row_ptr, x.col_idx, s, directed=d)[0])
+        G.close()
+
+
+def test_the_host_loop_where_the_scratch_does_not_fit():
+    g = gg.erdos_renyi(50000, 4, seed=47)  # 512 units of 2.2 MB
+    some = gg.sample_sources(g, 50, seed=48)
+    src = np.tile(some, 11)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        with _LittleMemory(640 << 20):
+            got = run_mode(G, src, bcm.BC_MODE_AUTO)
+        check_bc(got, 11.0 * oracle_bc(g, some))
