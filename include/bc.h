@@ -452,7 +452,7 @@ bc_status bc_set_work_items(bc_graph_t g, int32_t group_cut, int32_t chunk);
  *
  * bc_sssp writes dist_dev [n] (device, int32, caller vertex order): the
  * distance from `source`, -1 where unreachable, complete when the call
- * returns (it waits on `stream` once per 8 queued passes).  Calls on one graph
+ * returns (it waits on `stream` once per 8 to 32 queued passes).  Calls on one graph
  * are serialised (one workspace per graph).  Errors: BC_ERR_INVALID_ARG,
  * BC_ERR_OUT_OF_MEMORY, BC_ERR_DEVICE.
  */

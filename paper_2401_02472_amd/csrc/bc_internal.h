@@ -414,9 +414,11 @@ hipError_t pagerank_init(const PrDev &d, int32_t max_iter, hipStream_t stream);
 hipError_t pagerank_pull(const PrDev &d, int32_t iter, hipStream_t stream);
 hipError_t pagerank_finish(const PrDev &d, int32_t iter, hipStream_t stream);
 
-hipError_t sssp_init(const SsspDev &d, int32_t src, SsspSlot *left, hipStream_t stream);
-hipError_t sssp_pass(const SsspDev &d, int32_t pass, SsspSlot *left, int32_t *quiet,
+hipError_t sssp_init(const SsspDev &d, int32_t src, SsspSlot *left, int32_t *flags,
                      hipStream_t stream);
+hipError_t sssp_pass(const SsspDev &d, int32_t pass, SsspSlot *left, int32_t *chose,
+                     hipStream_t stream);
+hipError_t sssp_fold(int32_t pass, SsspSlot *left, int32_t *pending, hipStream_t stream);
 hipError_t sssp_export(int32_t n, const int32_t *perm, const int32_t *dist, int32_t *out,
                        hipStream_t stream);
 hipError_t permute_arc_values(int32_t n, int64_t nnz, const int32_t *old_rp,

@@ -77,14 +77,16 @@ bc_status bc_sssp(bc_graph_t g, int32_t source, int32_t *dist_dev, void *stream_
     // passes queued per host poll: 8, 12, 18, ... 32 (a poll takes 40 us, about
     // as much as 9 passes that find nothing to do)
     constexpr int64_t kFirst = 8, kMost = 32;
+    // a call that has made no choice in this many passes makes none after them
+    constexpr int64_t kUndecided = 20;
     if (!w.dist) {
         hipError_t e = hipMalloc(&w.dist, (size_t)g->n * sizeof(int32_t));
         if (e == hipSuccess) e = hipMalloc(&w.stamp, (size_t)g->n * sizeof(int32_t));
-        if (e == hipSuccess) e = hipMalloc(&w.flags, kMost * sizeof(int32_t));
+        if (e == hipSuccess) e = hipMalloc(&w.flags, 2 * sizeof(int32_t));
         if (e == hipSuccess) e = hipMalloc(&w.slots, 3 * kSsspSlots * sizeof(SsspSlot));
         if (e == hipSuccess) e = hipMalloc(&w.d_stats, kStatWords * sizeof(unsigned long long));
         if (e == hipSuccess)
-            e = hipHostMalloc((void **)&w.h_flags, kMost * sizeof(int32_t), hipHostMallocDefault);
+            e = hipHostMalloc((void **)&w.h_flags, 2 * sizeof(int32_t), hipHostMallocDefault);
         if (e != hipSuccess) {
             if (w.dist) (void)hipFree(w.dist);
             if (w.stamp) (void)hipFree(w.stamp);
@@ -121,29 +123,36 @@ bc_status bc_sssp(bc_graph_t g, int32_t source, int32_t *dist_dev, void *stream_
     d.stamp = w.stamp;
     hipError_t e = hipSuccess;
     if (prof) e = hipMemsetAsync(w.d_stats, 0, kStatWords * sizeof(unsigned long long), stream);
-    if (e == hipSuccess) e = sssp_init(d, g->h_perm[(size_t)source], w.slots, stream);
+    if (e == hipSuccess) e = sssp_init(d, g->h_perm[(size_t)source], w.slots, w.flags, stream);
     bool done = false;
-    for (int64_t p0 = 1, K = kFirst; e == hipSuccess && !done; p0 += K, K = std::min(K + K / 2, kMost)) {
+    int32_t *const chose = w.flags, *const pending = w.flags + 1;
+    for (int64_t p0 = 1, K = kFirst; e == hipSuccess && !done;) {
         // every pass takes the pending vertices of smallest distance, which is
         // final: more passes than vertices cannot happen
         if (p0 > (int64_t)g->n + kMost) {
             e = hipErrorUnknown;
             break;
         }
-        e = hipMemsetAsync(w.flags, 0, K * sizeof(int32_t), stream);
         for (int32_t p = (int32_t)p0; p < p0 + K && e == hipSuccess; ++p) {
             const bool m = prof && (p - 1) % stride == 0;
             timer.on = m;
             d.stats = m ? w.d_stats + 9 : nullptr;
             e = timer.begin(BC_PROF_SSSP, stream);
-            if (e == hipSuccess) e = sssp_pass(d, p, w.slots, w.flags + (p - p0), stream);
+            if (e == hipSuccess) e = sssp_pass(d, p, w.slots, chose, stream);
             if (e == hipSuccess) e = timer.end(stream);
         }
+        p0 += K;
+        if (e == hipSuccess) e = sssp_fold((int32_t)(p0 - 1), w.slots, pending, stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(w.h_flags, w.flags, K * sizeof(int32_t), hipMemcpyDeviceToHost,
+            e = hipMemcpyAsync(w.h_flags, w.flags, 2 * sizeof(int32_t), hipMemcpyDeviceToHost,
                                stream);
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
-        for (int32_t q = 0; q < K && e == hipSuccess; ++q) done |= w.h_flags[q] != 0;
+        done = e == hipSuccess && w.h_flags[1] == 0;
+        // a narrow front (a road network's) never has much pending: the books
+        // that a choice needs go (4M-vertex grid 5.4 -> 3.5 ms, without
+        // shortcuts 71 -> 50; 2.4M vertices 3.8 -> 2.6)
+        if (d.split >= 0 && p0 > kUndecided && w.h_flags[0] == 0) d.split = -1;
+        K = std::min(K + K / 2, kMost);
     }
     if (e == hipSuccess) e = sssp_export(g->n, g->d_perm, w.dist, dist_dev, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);

@@ -263,7 +263,7 @@ struct bc_graph_s {
     std::mutex sssp_mu;
     struct Sssp {
         int32_t *dist = nullptr, *stamp = nullptr;
-        int32_t *flags = nullptr;                 // per queued pass: it found nothing pending
+        int32_t *flags = nullptr;                 // [2]: a pass chose, something is pending
         bcx::SsspSlot *slots = nullptr;
         int32_t *h_flags = nullptr;               // pinned mirror of the flags
         unsigned long long *d_stats = nullptr;    // kStatWords counters ([9..11] used)

@@ -101,8 +101,8 @@ __device__ __forceinline__ int32_t weight_of(const SsspDev &d, int32_t e) {
 
 // One pass.  left: three sets of slots, of which pass p reads the one of pass
 // p - 1, adds to its own and clears the one of pass p + 1.  A pass that finds
-// nothing pending sets *quiet and returns at once, so that several passes can
-// be queued without a host wait.
+// nothing pending returns at once, so that several passes can be queued without
+// a host wait.  *chose is set by a pass that leaves vertices to later ones.
 //
 // A wave looks at 64 chunk items at once, one per lane, and then relaxes the
 // pending ones with all 64 lanes, the next item's columns and weights loading
@@ -117,7 +117,7 @@ __device__ __forceinline__ int32_t weight_of(const SsspDev &d, int32_t e) {
 template <bool kSplit>
 __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d, int32_t pass,
                                                                       SsspSlot *left,
-                                                                      int32_t *quiet) {
+                                                                      int32_t *chose) {
     __shared__ int32_t hub[kSplit ? kHubs : 1];
     const int lane = lane_id();
     const SsspSlot *prev = left + (pass + 2) % 3 * kSsspSlots;
@@ -136,11 +136,9 @@ __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d,
         due = shfl64(due, 0);
         key = __shfl(key, 0);
     }
-    if (due == 0) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) *quiet = 1;
-        return;
-    }
+    if (due == 0) return;
     const bool split = kSplit && (int64_t)due > d.split;
+    if (split && blockIdx.x == 0 && threadIdx.x == 0) *chose = 1;
     const int64_t cut = split ? (int64_t)kInf - key + d.delta : kInf;
     const int32_t limit = (int32_t)min(cut, (int64_t)kInf);  // distances below it are taken
     int32_t hubs = 0;
@@ -215,7 +213,10 @@ __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d,
     // 64 vertices of degree 1 to 64: the arcs of the pending ones, flattened.
     // The stamps of the wave's next kGroups groups load together.
     const uint32_t groups = (uint32_t)((d.live_end - d.big_end + kWave - 1) / kWave);
-    for (uint32_t g0 = wave; g0 < groups; g0 += kGroups * nwaves) {
+    // (dealt on from where the items end, so that few waves get both)
+    const uint32_t after = d.items % nwaves;
+    const uint32_t gwave = wave >= after ? wave - after : wave + nwaves - after;
+    for (uint32_t g0 = gwave; g0 < groups; g0 += kGroups * nwaves) {
         uint32_t mine = 0;  // bit q: the lane's vertex of group q is pending
 #pragma unroll
         for (int q = 0; q < kGroups; ++q) {
@@ -322,9 +323,25 @@ __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d,
     }
 }
 
+// What the passes so far left to the next one, in slot 0 alone (a pass without
+// kSplit looks at no other), and for the host: flags[0] = something is pending.
+__global__ __launch_bounds__(kSsspSlots) void k_sssp_fold(SsspSlot *set, int32_t *flags) {
+    unsigned long long work = set[threadIdx.x].work;
+    uint32_t key = set[threadIdx.x].key;
+#pragma unroll
+    for (int off = kSsspSlots / 2; off >= 1; off >>= 1) {
+        work += __shfl_xor(work, off);
+        key = max(key, __shfl_xor(key, off));
+    }
+    const bool first = threadIdx.x == 0;
+    set[threadIdx.x] = SsspSlot{first ? work : 0, first ? key : 0, {}};
+    if (first) flags[0] = work != 0 ? 1 : 0;
+}
+
 // Distances and stamps for pass 1; its predecessor's slots say "one arc, at 0".
-__global__ void k_sssp_init(SsspDev d, int32_t src, SsspSlot *left) {
+__global__ void k_sssp_init(SsspDev d, int32_t src, SsspSlot *left, int32_t *flags) {
     const int32_t at = blockIdx.x * blockDim.x + threadIdx.x, all = gridDim.x * blockDim.x;
+    if (at < 2) flags[at] = 0;
     for (int32_t i = at; i < 3 * kSsspSlots; i += all)
         left[i] = SsspSlot{i == 0, i == 0 ? (uint32_t)kInf : 0, {}};
     for (int32_t v = at; v < d.n; v += all) {
@@ -370,18 +387,26 @@ int blocks_for(int64_t n) {
 unsigned int exec_partial_sssp() { return exec_partial_take(); }
 #endif
 
-hipError_t sssp_init(const SsspDev &d, int32_t src, SsspSlot *left, hipStream_t stream) {
-    hipLaunchKernelGGL(k_sssp_init, dim3(blocks_for(d.n)), dim3(kBlock), 0, stream, d, src, left);
+hipError_t sssp_init(const SsspDev &d, int32_t src, SsspSlot *left, int32_t *flags,
+                     hipStream_t stream) {
+    hipLaunchKernelGGL(k_sssp_init, dim3(blocks_for(d.n)), dim3(kBlock), 0, stream, d, src, left,
+                       flags);
     return hipGetLastError();
 }
 
-hipError_t sssp_pass(const SsspDev &d, int32_t pass, SsspSlot *left, int32_t *quiet,
+hipError_t sssp_pass(const SsspDev &d, int32_t pass, SsspSlot *left, int32_t *chose,
                      hipStream_t stream) {
     const int64_t groups = (d.live_end - d.big_end + kWave - 1) / kWave;
     int64_t blocks = (d.items + groups + kWavesPerBlock - 1) / kWavesPerBlock;
     blocks = blocks < 1 ? 1 : (blocks > kMaxGridBlocks ? kMaxGridBlocks : blocks);
     auto k = d.split >= 0 ? k_sssp_pass<true> : k_sssp_pass<false>;
-    hipLaunchKernelGGL(k, dim3((int)blocks), dim3(kBlock), 0, stream, d, pass, left, quiet);
+    hipLaunchKernelGGL(k, dim3((int)blocks), dim3(kBlock), 0, stream, d, pass, left, chose);
+    return hipGetLastError();
+}
+
+hipError_t sssp_fold(int32_t pass, SsspSlot *left, int32_t *pending, hipStream_t stream) {
+    hipLaunchKernelGGL(k_sssp_fold, dim3(1), dim3(kSsspSlots), 0, stream,
+                       left + pass % 3 * kSsspSlots, pending);
     return hipGetLastError();
 }
 

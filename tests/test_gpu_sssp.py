@@ -73,6 +73,25 @@ def test_sssp_passes_by_distance(g, lo, hi):
             assert np.array_equal(gpu_dist(G, s), want)
 
 
+@pytest.mark.parametrize("tail", [7, 8, 19, 20, 21, 40, 300])
+def test_sssp_narrow_front_before_and_after_a_wide_one(tail):
+    """A path into a graph with enough arcs for the choice by distance: from its
+    far end the front is narrow for `tail` passes, past which the books are
+    given up from the 20th on; from inside it is wide at first."""
+    g = gg.erdos_renyi(150_000, 16, seed=9)
+    src = np.repeat(np.arange(g.n), np.diff(g.row_ptr))
+    ends = g.n + np.arange(tail)
+    u = np.concatenate([src, [5], ends[:-1]])
+    v = np.concatenate([g.col_idx, ends[:1], ends[1:]])
+    g = gg.csr_from_edges(g.n + tail, u, v)
+    w = gg.edge_weights(g, seed=10)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        G.set_weights(w)
+        for s in (g.n - 1, 77):
+            want, _ = oracle.sssp(g.row_ptr, g.col_idx, w, s)
+            assert np.array_equal(gpu_dist(G, s), want)
+
+
 def test_sssp_largest_distance():
     """The arc back from the farthest vertex would pass the range of int32."""
     g = gg.path(3)
