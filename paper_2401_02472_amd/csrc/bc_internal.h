@@ -373,6 +373,7 @@ struct SsspDev {
     // within delta of the smallest (-1: every pass takes all)
     int64_t split;
     int32_t delta;
+    int32_t wait;  // with split -1: stamp the improvements found, not the tries
     uint32_t items;
     const int32_t *row_ptr;
     const int32_t *col_idx;

@@ -260,6 +260,7 @@ struct bc_graph_s {
     // every arc weighs 1) and a workspace used by one call at a time
     int32_t *d_weight = nullptr;
     int32_t max_weight = 1;
+    bool even_weights = true;  // every arc weighs the same
     std::mutex sssp_mu;
     struct Sssp {
         int32_t *dist = nullptr, *stamp = nullptr;

@@ -61,36 +61,39 @@ __device__ __forceinline__ uint32_t about_arcs(const SsspDev &d, int32_t v) {
 // the minimum first: a hub that thousands of vertices improve at once sees
 // one atomic from a workgroup for each new minimum there (346 -> 26 us for the
 // pass that reaches the hubs of the scale-22 R-MAT).  Loads and atomics of
-// all arcs are issued together.
-template <bool kSplit, int kArcs>
+// kTogether arcs are issued together.
+template <bool kWait, int kTogether, int kArcs>
 __device__ __forceinline__ void relax(const SsspDev &d, int32_t *hub, int32_t hubs,
                                       const int32_t (&nb)[kArcs], const int32_t (&nd)[kArcs],
                                       int32_t pass, Relax &r) {
     int32_t old[kArcs];
 #pragma unroll
-    for (int u = 0; u < kArcs; ++u) {
-        old[u] = -1;
-        if (nb[u] >= hubs) old[u] = d.dist[nb[u]];
-        else if (nb[u] >= 0 && nd[u] < hub[nb[u]]) old[u] = atomicMin(&hub[nb[u]], nd[u]);
-    }
-    // kSplit: wait for the distance found, so that only the improvements are
-    // stamped (there are more tries than those on graphs with hubs).  Without
-    // it every try is stamped, which is right too: a distance above nd was
-    // read, so someone improved the vertex in this pass (the 1M-vertex grid
-    // 1.67 -> 1.45 ms; the scale-22 R-MAT the other way 2.10 -> 2.15).
+    for (int at = 0; at < kArcs; at += kTogether) {
 #pragma unroll
-    for (int u = 0; u < kArcs; ++u) {
-        if (nd[u] < old[u]) {
-            if (kSplit || d.stats) old[u] = atomicMin(&d.dist[nb[u]], nd[u]);
-            else atomicMin(&d.dist[nb[u]], nd[u]);
+        for (int u = at; u < at + kTogether; ++u) {
+            old[u] = -1;
+            if (nb[u] >= hubs) old[u] = d.dist[nb[u]];
+            else if (nb[u] >= 0 && nd[u] < hub[nb[u]]) old[u] = atomicMin(&hub[nb[u]], nd[u]);
         }
-    }
+        // kWait: wait for the distance found, so that only the improvements are
+        // stamped (there are more tries than those on graphs with hubs).  Without
+        // it every try is stamped, which is right too: a distance above nd was
+        // read, so someone improved the vertex in this pass (the 1M-vertex grid
+        // 1.67 -> 1.45 ms; the scale-22 R-MAT the other way 2.10 -> 2.15).
 #pragma unroll
-    for (int u = 0; u < kArcs; ++u) {
-        if (nd[u] < old[u]) {
-            d.stamp[nb[u]] = pass + 1;
-            r.leave(about_arcs(d, nb[u]), nd[u]);
-            ++r.better;
+        for (int u = at; u < at + kTogether; ++u) {
+            if (nd[u] < old[u]) {
+                if (kWait || d.stats) old[u] = atomicMin(&d.dist[nb[u]], nd[u]);
+                else atomicMin(&d.dist[nb[u]], nd[u]);
+            }
+        }
+#pragma unroll
+        for (int u = at; u < at + kTogether; ++u) {
+            if (nd[u] < old[u]) {
+                d.stamp[nb[u]] = pass + 1;
+                r.leave(about_arcs(d, nb[u]), nd[u]);
+                ++r.better;
+            }
         }
     }
 }
@@ -114,11 +117,18 @@ __device__ __forceinline__ int32_t weight_of(const SsspDev &d, int32_t e) {
 // each a 4-byte atomic and a 4-byte store at random, bound those.  Before, with
 // every pass taking all: 11 passes, 3 times every arc, 42M improvements, 2.4 ms.
 // The waves per SIMD asked for: 1M-vertex grid 1.43 ms with 8, 1.56 with 6.
-template <bool kSplit>
+//
+// Three forms: kSplit, where a pass may choose; without it, and kWait, large
+// graphs of even weights, which relax one arc after the other, as a level's
+// arcs all offer the same distance and later ones find it there (scale-16
+// R-MAT 0.21 -> 0.17 ms, scale 20 0.37, where kSplit takes 0.55); and
+// neither, small graphs and narrow fronts.
+template <bool kSplit, bool kWait>
 __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d, int32_t pass,
                                                                       SsspSlot *left,
                                                                       int32_t *chose) {
     __shared__ int32_t hub[kSplit ? kHubs : 1];
+    constexpr bool kSerial = kWait && !kSplit;
     const int lane = lane_id();
     const SsspSlot *prev = left + (pass + 2) % 3 * kSsspSlots;
     SsspSlot *cur = left + pass % 3 * kSsspSlots;
@@ -202,7 +212,7 @@ __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d,
                 // (saturated: the farthest vertex's arcs may pass the range)
                 w[u] = (int32_t)min((uint32_t)from + (uint32_t)w[u], (uint32_t)kInf);
             }
-            relax<kSplit, kPerLane>(d, hub, hubs, c, w, pass, r);
+            relax<kWait, kSerial ? 1 : kPerLane>(d, hub, hubs, c, w, pass, r);
 #pragma unroll
             for (int u = 0; u < kPerLane; ++u) {
                 c[u] = c2[u];
@@ -266,7 +276,7 @@ __global__ __launch_bounds__(kBlock, kSplit ? 6 : 8) void k_sssp_pass(SsspDev d,
                         }
                     }
                 }
-                relax<kSplit, kRuns>(d, hub, hubs, c, w, pass, r);
+                relax<kWait, kSerial ? 1 : kRuns>(d, hub, hubs, c, w, pass, r);
             }
         }
     }
@@ -399,7 +409,8 @@ hipError_t sssp_pass(const SsspDev &d, int32_t pass, SsspSlot *left, int32_t *ch
     const int64_t groups = (d.live_end - d.big_end + kWave - 1) / kWave;
     int64_t blocks = (d.items + groups + kWavesPerBlock - 1) / kWavesPerBlock;
     blocks = blocks < 1 ? 1 : (blocks > kMaxGridBlocks ? kMaxGridBlocks : blocks);
-    auto k = d.split >= 0 ? k_sssp_pass<true> : k_sssp_pass<false>;
+    auto k = d.split >= 0 ? k_sssp_pass<true, true>
+                          : (d.wait ? k_sssp_pass<false, true> : k_sssp_pass<false, false>);
     hipLaunchKernelGGL(k, dim3((int)blocks), dim3(kBlock), 0, stream, d, pass, left, chose);
     return hipGetLastError();
 }
