@@ -107,7 +107,7 @@ typedef struct bc_options {
                             the frontier's neighbours) instead of scanning every
                             unvisited vertex; 1..2^20, -1 = never, 0 = the graph's
                             setting (bc_autotune's choice, else 64, or never for up to
-                            131,072 vertices)                                           */
+                            131,072 vertices and 2^25 arcs)                              */
     int32_t concurrency; /* batched mode: batches run at once, each with its own
                             workspace and stream, 1..8 (0 = by workspace size: 4 up to
                             1 GB, 2 up to 16 GB, else 1); BC is the sum of the parts in

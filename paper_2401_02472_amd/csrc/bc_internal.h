@@ -109,11 +109,15 @@ constexpr int kFineGroups = 8192;
 // Default threshold of the batched forward step: a level whose frontier has
 // fewer than nnz / kDefaultSparseDiv arcs expands from the frontier.
 constexpr int kDefaultSparseDiv = 64;
-// Graphs of up to kNoSparseN vertices take the scan-all step only: scanning
-// them costs less than the three more launches of a level (host loop, 64
-// sources, ms with / without the choice: R-MAT scale 16 1.02 / 0.85, 17 1.77 /
-// 1.55, 18 1.95 / 1.83, uniform random 50K 1.11 / 1.06, 200K 2.39 / 2.46).
+// Graphs of up to kNoSparseN vertices and kNoSparseArcs arcs take the scan-all
+// step only: scanning them costs less than the three more launches of a level
+// (host loop, 64 sources, ms with / without the choice: R-MAT scale 16 1.02 /
+// 0.85, 17 1.77 / 1.55, 18 1.95 / 1.83, uniform random 50K 1.11 / 1.06, 200K
+// 2.39 / 2.46; by arcs, scale 17 with 20M 3.10 / 2.94, 35M 5.17 / 5.10 and of 200
+// sources 13.1 / 13.6, uniform random 100K vertices with 50M 7.29 / 7.48, of 16
+// sources 4.95 / 5.24).
 constexpr int32_t kNoSparseN = 1 << 17;
+constexpr int64_t kNoSparseArcs = 1 << 25;
 // Most batches one call runs at once (each with its own workspace and stream).
 constexpr int kMaxParts = 8;
 

@@ -408,7 +408,7 @@ bc_status bc_create_graph(int32_t n, const int32_t *row_ptr, const int32_t *col_
     }
     g->device_bytes = (directed ? 2 : 1) * (rp_bytes + ci_bytes) + 2 * pm_bytes;
     reset_bc_items(g);
-    if (n <= kNoSparseN) g->tuned_sparse_div.store(-1);
+    g->tuned_sparse_div.store(untuned_sparse_div(g));
     // a graph of few 64-vertex groups takes finer host-loop work items
     if (n > 0 && (n + kWave - 1) / kWave < kFineGroups) {
         const bc_status st = set_bc_items(g, kFineCut, kFineChunk);

@@ -431,6 +431,10 @@ void free_graph_arrays(bc_graph_s *g);
 // pooled batched workspace (their partial rows follow the item count).  No run
 // on g may be in flight.
 bc_status set_bc_items(bc_graph_s *g, int32_t cut, int32_t chunk);
+// The sparse_div of a graph that is not tuned.
+inline int32_t untuned_sparse_div(const bc_graph_s *g) {
+    return g->n <= kNoSparseN && g->nnz <= kNoSparseArcs ? -1 : kDefaultSparseDiv;
+}
 // ---- policy and argument checks (bc_capi.hip) ----
 void range_exceeded(bc_graph_s *g);
 bool use_batched(const bc_graph_s *g, const bc_options *opt, int32_t k);

@@ -229,7 +229,7 @@ bc_status bc_autotune(bc_graph_t g, const int32_t *sources, int32_t k, void *str
     // replaces the current choice only when it is more than 2 % faster (on
     // one sample batch, near-equal settings swap places from run to run).
     constexpr double kTuneMargin = 0.98;
-    const int32_t untuned = g->n <= kNoSparseN ? -1 : kDefaultSparseDiv;
+    const int32_t untuned = untuned_sparse_div(g);
     const int32_t divs[] = {untuned, untuned == -1 ? kDefaultSparseDiv : -1, 16, 256};
     double div_ms = 1e30;
     int32_t best_div = untuned;

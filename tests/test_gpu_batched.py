@@ -815,3 +815,21 @@ def test_uint32_sized_workspaces_widen_when_counts_pass_32_bits(conc):
         again = batched(G, src, concurrency=conc, level_loop=bcm.BC_LOOP_HOST)
         check_bc(again, want)
         check_bc(batched(G, src[:64], level_loop=bcm.BC_LOOP_HOST), oracle_bc(g, src[:64]))
+
+
+@pytest.mark.parametrize("n,deg,sparse", [(100_000, 350, True), (100_000, 16, False)])
+def test_untuned_frontier_step_by_vertices_and_arcs(n, deg, sparse):
+    """A graph of few vertices scans them all, unless its arcs are many: the
+    vertices examined tell which of the two settings an untuned call has."""
+    g = gg.erdos_renyi(n, deg, seed=51)
+    src = gg.sample_sources(g, 2, seed=52)
+    seen = {}
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx, bcm.BC_GRAPH_TRUST_SYMMETRIC) as G:
+        G.profile_enable(True)
+        for div in (0, 64, -1):
+            G.profile_read(reset=True)
+            got = batched(G, src, level_loop=bcm.BC_LOOP_HOST, sparse_div=div)
+            seen[div] = G.profile_read(reset=True)["forward"]["vertices"]
+            check_bc(got, oracle_bc(g, src))
+    assert seen[64] < seen[-1]
+    assert seen[0] == seen[64 if sparse else -1]
