@@ -111,9 +111,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_pull(PrDev d, int32_t iter, int
                     col[u] = -1;
                     if (b + u * kWave < e) {
                         const int32_t a = b + u * kWave + lane;
-                        
                         const int32_t x = d.col_idx_in[min(a, e - 1)];
-
                         col[u] = a < e ? x : -1;
                     }
                 }
@@ -164,9 +162,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_pull(PrDev d, int32_t iter, int
                 for (int u = 0; u < kPerLane; ++u) {
                     const int32_t a = b + (u << lg);
                     c[u] = -1;
-                    
                     if (a < e) c[u] = d.col_idx_in[a];
-
                 }
                 double x[kPerLane];
 #pragma unroll

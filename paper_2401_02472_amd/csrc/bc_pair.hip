@@ -433,7 +433,7 @@ __global__ __launch_bounds__(kDeepBlock) void k_deep_forward(PairDev d) {
                         if (got[u]) q[mine++] = a.nb[u];
                 }
                 BC_FULL_EXEC();
-            if (__ballot(a.e < a.re) == 0ull) break;
+                if (__ballot(a.e < a.re) == 0ull) break;
                 next_arcs(d.g, a);
             }
             if (v >= 0) {
