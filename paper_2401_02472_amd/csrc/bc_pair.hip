@@ -28,7 +28,7 @@
 // level where they are narrow.  Road-like grids of 1M vertices against the
 // batched kernels: without shortcuts (1,700 levels, counts past double's
 // range), 50 sources 238 -> 17.4 ms; with shortcuts (122 levels), 64 sources
-// 23.9 -> 13.2 ms.
+// 23.9 -> 12.2 ms.
 //
 // Forward: a vertex is claimed by an atomic AND on its code; a workgroup
 // collects its claims in LDS and takes their queue places with one atomic on
@@ -122,15 +122,22 @@ __device__ __forceinline__ uint32_t entry_mask(int32_t x) { return (uint32_t)x >
 // x 2^e, exact unless it leaves double's range.
 __device__ __forceinline__ double scaled(double x, int32_t e) { return e ? ldexp(x, e) : x; }
 
-// Forward step of level L.  Block b works for source b mod k (the same
-// sources' blocks land on the same XCD when k is a multiple of 8) on the
-// 256-pair pieces b / k, b / k + per, ... of its level.
+// Block b of a level step works for source b mod turns(k) on the pieces
+// b / turns(k), b / turns(k) + per, ... of 256 pairs of its level.  Not a multiple
+// of eight, so that a source's blocks go round the XCDs: with all of them on one,
+// as workgroups are dealt, an XCD waits for the sources whose levels are wide (ms
+// per source, 1M-vertex grid with shortcuts: 63 or 65 sources 0.191, 64 0.224; 4M
+// vertices 31 or 33 0.74, 32 0.91).
+__host__ __device__ inline int32_t turns(int32_t k) { return k % 8 == 0 ? k + 1 : k; }
+
+// Forward step of level L.
 template <bool kExt>
 __global__ __launch_bounds__(kBlock) void k_pair_forward(PairDev d, int32_t L, int32_t per) {
     __shared__ int32_t found[kBlock * kPairMaxDeg];
     __shared__ int32_t nfound, place;
-    const int32_t s = (int32_t)(blockIdx.x % (uint32_t)d.k);
-    const int32_t piece = (int32_t)(blockIdx.x / (uint32_t)d.k);
+    const int32_t s = (int32_t)(blockIdx.x % (uint32_t)turns(d.k));
+    const int32_t piece = (int32_t)(blockIdx.x / (uint32_t)turns(d.k));
+    if (s >= d.k) return;
     const Segment sg = segment(d, L, s);
     const int t = threadIdx.x;
     if (piece == 0 && t == 0) {
@@ -259,9 +266,9 @@ __global__ __launch_bounds__(kBlock) void k_pair_forward(PairDev d, int32_t L, i
 // Reverse step of level L >= 1.
 template <bool kExt>
 __global__ __launch_bounds__(kBlock) void k_pair_reverse(PairDev d, int32_t L, int32_t per) {
-    const int32_t s = (int32_t)(blockIdx.x % (uint32_t)d.k);
-    const int32_t piece = (int32_t)(blockIdx.x / (uint32_t)d.k);
-    if (L > d.depth[s]) return;
+    const int32_t s = (int32_t)(blockIdx.x % (uint32_t)turns(d.k));
+    const int32_t piece = (int32_t)(blockIdx.x / (uint32_t)turns(d.k));
+    if (s >= d.k || L > d.depth[s]) return;
     const Segment sg = segment(d, L, s);
     const bool leaf = L == d.depth[s];
     const int child = (L + 1) % 3;
@@ -638,13 +645,13 @@ hipError_t pair_start(const PairDev &d, hipStream_t stream) {
 }
 
 hipError_t pair_forward(const PairDev &d, int32_t level, int32_t per, hipStream_t stream) {
-    hipLaunchKernelGGL(d.ex ? k_pair_forward<true> : k_pair_forward<false>, dim3(d.k * per),
+    hipLaunchKernelGGL(d.ex ? k_pair_forward<true> : k_pair_forward<false>, dim3(turns(d.k) * per),
                        dim3(kBlock), 0, stream, d, level, per);
     return hipGetLastError();
 }
 
 hipError_t pair_reverse(const PairDev &d, int32_t level, int32_t per, hipStream_t stream) {
-    hipLaunchKernelGGL(d.ex ? k_pair_reverse<true> : k_pair_reverse<false>, dim3(d.k * per),
+    hipLaunchKernelGGL(d.ex ? k_pair_reverse<true> : k_pair_reverse<false>, dim3(turns(d.k) * per),
                        dim3(kBlock), 0, stream, d, level, per);
     return hipGetLastError();
 }
