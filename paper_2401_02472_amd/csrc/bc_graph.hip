@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kBlock) void k_probe_seed(int32_t n, int32_t live, 
             if (v == (int32_t)((int64_t)live * j / 4)) x |= 1u << (8 * j);
         word[v] = x;
     }
-    for (int32_t i = at; i < steps; i += all) found[i] = 0;
+    for (int32_t i = at; i < steps + 4; i += all) found[i] = 0;
 }
 
 // Level L + 1 of the four: a vertex takes it where a neighbour is at level L.
@@ -74,6 +74,21 @@ __global__ __launch_bounds__(kBlock) void k_probe_step(int32_t n, int32_t L, con
     if (any) found[L] = 1;
 }
 
+// count[j] += vertices that search j has reached.
+__global__ __launch_bounds__(kBlock) void k_probe_count(int32_t n, const uint32_t *word,
+                                                        int32_t *count) {
+    int32_t mine[4] = {};
+    for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x)
+        for (int j = 0; j < 4; ++j) mine[j] += (word[v] >> (8 * j) & 255u) != 0u;
+    __shared__ int32_t sum[4];
+    if (threadIdx.x < 4) sum[threadIdx.x] = 0;
+    __syncthreads();
+    for (int j = 0; j < 4; ++j)
+        if (mine[j]) atomicAdd(&sum[j], mine[j]);
+    __syncthreads();
+    if (threadIdx.x < 4 && sum[threadIdx.x]) atomicAdd(&count[threadIdx.x], sum[threadIdx.x]);
+}
+
 int grid_for(int64_t items) {
     int64_t g = (items + kBlock - 1) / kBlock;
     return (int)(g < 1 ? 1 : (g > 4096 ? 4096 : g));
@@ -98,6 +113,8 @@ hipError_t depth_probe(int32_t n, int32_t live, const int32_t *row_ptr, const in
     for (int32_t L = 0; L < steps; ++L)
         hipLaunchKernelGGL(k_probe_step, dim3(grid_for(n)), dim3(kBlock), 0, stream, n, L, row_ptr,
                            col_idx, word, found);
+    hipLaunchKernelGGL(k_probe_count, dim3(std::min(grid_for(n), 512)), dim3(kBlock), 0, stream, n,
+                       word, found + steps);
     return hipGetLastError();
 }
 

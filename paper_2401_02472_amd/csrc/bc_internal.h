@@ -438,8 +438,8 @@ hipError_t relabel_csr(int32_t n, int64_t nnz, const int32_t *old_rp, const int3
                        const int32_t *new_rp, const int32_t *perm, const int32_t *iperm,
                        int32_t *new_ci, hipStream_t stream);
 // Breadth-first from the vertices live * j / 4 (j = 0 .. 3), `steps` levels of
-// an undirected graph: found[L] != 0 where one of them has a level L + 1.
-// word: [n] scratch.
+// an undirected graph: found[L] != 0 where one of them has a level L + 1, and
+// found[steps + j] the vertices that search j reached.  word: [n] scratch.
 hipError_t depth_probe(int32_t n, int32_t live, const int32_t *row_ptr, const int32_t *col_idx,
                        int32_t steps, uint32_t *word, int32_t *found, hipStream_t stream);
 // dst[o] = src[perm[o]] for o < n (internal order -> caller order).

@@ -67,39 +67,50 @@ __global__ void k_lay_nest(int32_t n, const int32_t *inner, int32_t *size, int32
     }
 }
 
-// x[i] becomes the sum of the entries before it (one block); x[n] the total.
-__global__ __launch_bounds__(kScanBlock) void k_lay_scan(int32_t n, int32_t *x) {
-    constexpr int kPer = 16, kWaves = kScanBlock / kWave;
-    __shared__ uint32_t part[kWaves];
+// x[i] becomes the sum of the entries before it among a block's `span`; the
+// block's total goes to part[block], or to x[n] where one block takes all.
+constexpr int kScanPer = 16, kScanSpan = kScanBlock * kScanPer;
+__global__ __launch_bounds__(kScanBlock) void k_lay_scan(int32_t n, int32_t span, int32_t *x,
+                                                         int32_t *part) {
+    constexpr int kWaves = kScanBlock / kWave;
+    __shared__ uint32_t wave_sum[kWaves];
     const int t = threadIdx.x, wave = t / kWave;
+    const int32_t from = blockIdx.x * span, to = min(n, from + span);
     uint32_t carry = 0;
-    for (int32_t a = 0; a < n; a += kScanBlock * kPer) {
-        const int32_t b = a + t * kPer;
-        uint32_t y[kPer], mine = 0;
+    for (int32_t a = from; a < to; a += kScanSpan) {
+        const int32_t b = a + t * kScanPer;
+        uint32_t y[kScanPer], mine = 0;
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            y[j] = b + j < n ? (uint32_t)x[b + j] : 0u;
+        for (int j = 0; j < kScanPer; ++j) {
+            y[j] = b + j < to ? (uint32_t)x[b + j] : 0u;
             mine += y[j];
         }
         uint32_t sum;
         uint32_t run = wave_excl_scan(mine, sum);
-        if (lane_id() == 0) part[wave] = sum;
+        if (lane_id() == 0) wave_sum[wave] = sum;
         __syncthreads();
         uint32_t all = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
             if (w == wave) run += carry + all;
-            all += part[w];
+            all += wave_sum[w];
         }
 #pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            if (b + j < n) x[b + j] = (int32_t)run;
+        for (int j = 0; j < kScanPer; ++j) {
+            if (b + j < to) x[b + j] = (int32_t)run;
             run += y[j];
         }
         carry += all;
         __syncthreads();
     }
-    if (t == 0) x[n] = (int32_t)carry;
+    if (t == 0) (part ? part[blockIdx.x] : x[n]) = (int32_t)carry;
+}
+
+// The blocks' own scans of x put together: part holds the sums before them and,
+// behind those, the total.
+__global__ void k_lay_add(int32_t n, int32_t parts, int32_t *x, const int32_t *part) {
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i <= n; i += gridDim.x * blockDim.x)
+        x[i] = i < n ? x[i] + part[i / kScanSpan] : part[parts];
 }
 
 // pos[v]: v's place (its patches' places added up); its degree and its
@@ -163,10 +174,19 @@ hipError_t layout_build(const LayoutDev &d, hipStream_t stream) {
     hipLaunchKernelGGL(k_lay_count, grid, block, 0, stream, n, label[0], size[0]);
     hipLaunchKernelGGL(k_lay_nest, grid, block, 0, stream, n, label[0], size[0], label[1], size[1]);
     hipLaunchKernelGGL(k_lay_nest, grid, block, 0, stream, n, label[1], size[1], label[2], size[2]);
-    hipLaunchKernelGGL(k_lay_scan, dim3(1), dim3(kScanBlock), 0, stream, n, size[2]);
+    // (one block alone took 0.9 ms for a scan of 1M entries)
+    auto scan = [&](int32_t *x, int32_t *part) {
+        const int32_t parts = (n + kScanSpan - 1) / kScanSpan;
+        hipLaunchKernelGGL(k_lay_scan, dim3(parts), dim3(kScanBlock), 0, stream, n, kScanSpan, x,
+                           part);
+        hipLaunchKernelGGL(k_lay_scan, dim3(1), dim3(kScanBlock), 0, stream, parts, parts, part,
+                           nullptr);
+        hipLaunchKernelGGL(k_lay_add, grid, block, 0, stream, n, parts, x, part);
+    };
+    scan(size[2], d.pos);  // (pos is written after it)
     hipLaunchKernelGGL(k_lay_place, grid, block, 0, stream, n, d.row_ptr, d.iperm, label[0],
                        label[1], label[2], size[0], size[1], size[2], d.pos, d.new_rp, d.caller);
-    hipLaunchKernelGGL(k_lay_scan, dim3(1), dim3(kScanBlock), 0, stream, n, d.new_rp);
+    scan(d.new_rp, label[0]);  // (the labels have been read)
     hipLaunchKernelGGL(k_lay_arcs, grid, block, 0, stream, n, d.row_ptr, d.col_idx, d.pos,
                        d.new_rp, d.new_col, d.four);
     return hipGetLastError();

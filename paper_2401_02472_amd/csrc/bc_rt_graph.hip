@@ -421,18 +421,22 @@ bc_status bc_create_graph(int32_t n, const int32_t *row_ptr, const int32_t *col_
     if (pair_fits(g) && nnz > 0) {
         // (without room for the probe the graph is taken for a shallow one)
         uint32_t *word = nullptr;
-        int32_t *found = nullptr, last = 0;
+        int32_t *found = nullptr, last[5] = {};
         constexpr int32_t kSteps = kPairDepth + 1;
         e = hipMalloc(&word, (size_t)n * sizeof(uint32_t));
-        if (e == hipSuccess) e = hipMalloc(&found, kSteps * sizeof(int32_t));
+        if (e == hipSuccess) e = hipMalloc(&found, (kSteps + 4) * sizeof(int32_t));
         if (e == hipSuccess)
             e = depth_probe(n, g->live_end, g->d_row_ptr, g->d_col_idx, kSteps, word, found, st);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(&last, found + kSteps - 1, sizeof last, hipMemcpyDeviceToHost, st);
+            e = hipMemcpyAsync(last, found + kSteps - 1, sizeof last, hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (word) (void)hipFree(word);
         if (found) (void)hipFree(found);
-        g->deep = e == hipSuccess && last != 0;
+        g->deep = e == hipSuccess && last[0] != 0;
+        // a ball that grows as on a plane, from most sources to beyond the
+        // middle of the far side
+        const int32_t reached = std::max(*std::max_element(last + 1, last + 5), 1);
+        g->depth_guess = 1.6 * kSteps * std::sqrt((double)g->live_end / reached);
         if (e != hipSuccess) (void)hipGetLastError();
     }
     *out = g;

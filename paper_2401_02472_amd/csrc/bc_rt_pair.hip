@@ -51,11 +51,11 @@ static PairShape pair_shape(const bc_graph_s *g, int32_t k) {
     // 2.75 us per level, and 8.2 ns per pair of a source on its one compute
     // unit, 0.23 ns per pair over the device.  For instance, in ms, launches
     // against workgroups: 1024^2 with shortcuts (122 levels), 1 source 1.9 /
-    // 9.0, 64 sources 13.2 / 15.7; without shortcuts (1,700 levels), 64
+    // 9.0, 64 sources 12.2 / 15.7; without shortcuts (1,700 levels), 64
     // sources 31.6 / 18.7; 300^2 with shortcuts, 64 sources 2.2 / 1.1.
     const double n = (double)g->n, pairs = n * (double)k;
     const int32_t hint = g->pair_depth_hint.load();
-    const double levels = hint > 0 ? (double)hint : std::sqrt(n);
+    const double levels = hint > 0 ? (double)hint : g->depth_guess;
     const double launches = 0.5e-3 + levels * 11e-6 + pairs * 0.18e-9;
     const double alone = levels * 2.75e-6 +
                          std::max(n * 8.2e-9 * std::ceil((double)k / kCus), pairs * 0.23e-9);

@@ -301,6 +301,7 @@ struct bc_graph_s {
     // pair path (the choice is the graph's, not its calls', so that a call's
     // result does not depend on the calls before it)
     bool deep = false;
+    double depth_guess = 0;  // of a deep graph: its levels, before a run has told
     // pair-path runs keep exponents once a count passed double's range
     std::atomic<bool> pair_ext{false};
     // the pair path's vertex order and the CSR in it (built on first use, a
