@@ -273,8 +273,7 @@ struct SourceUnit {
     int32_t graph, first, count;
     double *row;       // [n]
     int32_t *q;        // [n]
-    double *sig;       // [n]
-    double *val;       // [n + 1], where the values do not fit LDS
+    double *sig;       // [n], and [n + 1] values from source_val on where LDS has no room
     uint32_t *lvl;     // [n + 2][kSrcClasses] level starts in the queues
     double *out;       // NULL, or the request's BC (caller order) written by this unit
     int32_t *dist;     // exports (caller order), NULL unless asked for:
@@ -291,6 +290,8 @@ struct SourceSum {
     double *out;
 };
 
+// Where a unit's values begin behind its sigmas (a multiple of 256 bytes).
+__host__ __device__ inline size_t source_val(int32_t n) { return ((size_t)n + 31) & ~(size_t)31; }
 // Whether the values of a graph of n vertices fit LDS, and a workgroup's LDS.
 bool source_in_lds(int32_t n);
 size_t source_lds_bytes(int32_t n);

@@ -41,6 +41,7 @@ int32_t source_unit(const bc_graph_s *g, int32_t k) {
 // Scratch of one unit: its BC row, queue, sigmas and level records.
 size_t source_unit_bytes(const bc_graph_s *g) {
     const size_t n = (size_t)std::max<int32_t>(g->n, 1);
+    static_assert(kAlign == 32 * sizeof(double), "source_val rounds up to kAlign bytes");
     return 2 * align_up(n * sizeof(double)) + align_up(n * sizeof(int32_t)) +
            align_up((n + 2) * kSrcClasses * sizeof(uint32_t)) +
            (source_in_lds(g->n) ? 0 : align_up((n + 1) * sizeof(double)));
@@ -287,9 +288,7 @@ bc_status source_jobs(const std::vector<SourceJob> &jobs, hipStream_t stream,
                     d.row = (double *)cut(n * sizeof(double));
                     d.q = (int32_t *)cut(n * sizeof(int32_t));
                     d.lvl = (uint32_t *)cut((n + 2) * kSrcClasses * sizeof(uint32_t));
-                    d.sig = (double *)cut(n * sizeof(double));
-                    d.val = source_in_lds(job.g->n) ? nullptr
-                                                    : (double *)cut((n + 1) * sizeof(double));
+                    d.sig = (double *)cut(n * sizeof(double));  // (the last of them)
                     d.out = un.count == rq.k ? rq.out : nullptr;
                     d.dist = job.dist;
                     d.sigma = job.sigma;

@@ -408,10 +408,10 @@ k_source(const SourceUnit *units, const SourceGraph *graphs, const int32_t *sour
     const int32_t words = (n + 32) / 32;  // bits of the vertices and of entry n
     s.seen = reinterpret_cast<uint32_t *>(lds);
     s.done = s.seen + words;
-    if constexpr (kMem) s.val = uniform(un.val);
-    else s.val = lds;
     s.q = uniform(un.q);
     s.sig = uniform(un.sig);
+    if constexpr (kMem) s.val = s.sig + source_val(n);
+    else s.val = lds;
     double *row = uniform(un.row);
     uint32_t *lvl = uniform(un.lvl);
     const int32_t first = uniform(un.first), count = uniform(un.count);
