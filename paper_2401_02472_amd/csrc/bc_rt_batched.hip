@@ -751,8 +751,8 @@ bc_status batched_run(bc_graph_s *g, const int32_t *sources, int32_t k, double *
 // lanes in the same order whatever else shares its batches: the whole batches
 // run first, then the shared ones, which the small requests and remainders
 // fill largest first, each into the first with room (the order of arrival took
-// five batches where three hold the requests 1, 8, 64, 1, 8, 64, 1, 7: 4.5
-// -> 2.4 ms on the 65K-vertex R-MAT).
+// five batches where three hold the requests 1, 8, 64, 1, 8, 64, 1, 7: 4.6
+// -> 2.9 ms on the 65K-vertex R-MAT).
 bc_status multi_run(bc_graph_s *g, const int32_t *sources, const int32_t *req_start,
                     int32_t nreq, double *const *outs, hipStream_t stream) {
     const int32_t k = req_start[nreq];

@@ -326,3 +326,23 @@ def test_autotune_times_the_loop_its_settings_belong_to(g):
             assert p["forward"]["launches"] > 0 and p["forward"]["vertices"] == 0
         G.profile_enable(False)
         check_bc(before, oracle_bc(g, src))
+
+
+@pytest.mark.parametrize("tail,deep", [(44, False), (45, True)])
+def test_where_a_graph_is_deep(tail, deep):
+    """A tree of fifteen children per vertex and four levels with a path at its
+    root: 4 + tail levels from a leaf, of which three of the four searches at
+    creation start."""
+    n = 54241
+    kids = np.arange(1, n)
+    ends = n + np.arange(tail)
+    g = gg.csr_from_edges(n + tail, np.concatenate([(kids - 1) // 15, [0], ends[:-1]]),
+                          np.concatenate([kids, ends[:1], ends[1:]]))
+    src = gg.sample_sources(g, 20, seed=29)
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx) as G:
+        G.profile_enable(True)
+        check_bc(_auto(G, src), oracle_bc(g, src))
+        p = G.profile_read(reset=True)
+        as_queues = (p["fused"]["launches"] == 0 and p["forward"]["vertices"] == 0
+                     and p["forward"]["launches"] > 0)
+        assert as_queues == deep
