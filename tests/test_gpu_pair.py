@@ -129,6 +129,27 @@ def test_profiled_run_of_several_rounds(case):
             assert p["reverse"]["owners"] == pairs - src.size
 
 
+def test_few_sources_past_a_group_share_the_round():
+    """22.0 MB per source: a round's 4 GB hold 194 sources of this graph, 24
+    groups of eight and two more, so 193 are one round.  A launch per level: a
+    second round would add at least half as many as the deepest source takes,
+    a source reaching at least half as far as any other."""
+    g = gg.grid_road(1024, 1024, 0.05, 0.001, seed=2)
+    src = gg.sample_sources(g, 193, seed=102)
+    launches = {}
+    with bcm.Graph(g.n, g.row_ptr, g.col_idx, bcm.BC_GRAPH_TRUST_SYMMETRIC) as G:
+        batched(G, src)  # the depth is known from here on
+        G.profile_enable(True)
+        for m in (192, 193):
+            G.profile_read(reset=True)
+            got = batched(G, src[:m])
+            p = G.profile_read(reset=True)
+            assert p["forward"]["vertices"] == 0, "not the pair path"
+            launches[m] = p["forward"]["launches"]
+    assert launches[192] <= launches[193] < 1.25 * launches[192]
+    check_bc(got, oracle_bc(g, src))
+
+
 def test_counts_beyond_double_range():
     """A lattice whose counts pass double's range: found on the way, run again
     with exponents, and with them from the start in later calls."""
