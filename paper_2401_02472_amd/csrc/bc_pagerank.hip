@@ -16,8 +16,8 @@
 // of the L2 (257 G gathers/s at most), and past the L2 81 G/s at 16 MB of
 // shares.  Where few vertices own many arcs, every workgroup keeps the shares
 // of the 20,352 highest-degree ones in its LDS: on the scale-22 R-MAT
-// (128M arcs, 42 % of them theirs) an iteration's pull takes 0.66 ms in place
-// of 0.88, with 24M lines from beyond the L2 at 4.6 TB/s; without that, the
+// (128M arcs, 42 % of them theirs) an iteration's pull takes 0.64 ms in place
+// of 0.88, with 22M lines from beyond the L2 at 4.4 TB/s; without that, the
 // same kernel 0.84.  Loads of the columns that bypass the caches made the
 // graphs whose columns fit the last-level cache slower (scale 20 0.127 ->
 // 0.172 ms) and gained nothing on the others.
